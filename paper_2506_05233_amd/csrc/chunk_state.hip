@@ -429,7 +429,10 @@ __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
 // T_s = sum over its chunks of the decayed updates, and the decay across it, D_s
 // (the product of its chunk decays).  The second starts every segment from the
 // state entering it, E_0 = 0 and E_{s+1} = D_s E_s + T_s -- the same chunk recurrence
-// applied to whole segments -- and walks the segment's chunks as above.
+// applied to whole segments -- and walks the segment's chunks as above.  A states-only call
+// needs no second walk: all its segments run side by side in the first launch and a small
+// kernel combines their totals (4 x 16 sequences of 4001 tokens, d 128: 140 us with the last
+// segment walked after the others, 78 us combined).
 constexpr int kWideThreads = 512;  // eight waves: two per SIMD
 
 // Segments of one launch of the wide scan.
@@ -439,7 +442,8 @@ struct SegPlan {
     int first;    // first segment this launch walks
     int count;    // segments this launch walks, per (sequence, part)
     bool totals;  // write T_s and D_s (first launch) instead of chunk and final states
-    float* tot;   // [B*H, total - 1, d_k (d_k + d_v)]: T_s of H as [R][c], then of G as [c][R]
+    int slots;    // segment totals kept per sequence: total - 1, or total when all are combined
+    float* tot;   // [B*H, slots, d_k (d_k + d_v)]: T_s of H, then of G (register order, see seg_total)
     float* dec;   // [B*H, total]: D_s
 };
 
@@ -679,7 +683,7 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
         // of thread tid at [(rt NCT + ct) kWideThreads + tid] * 4 + ii of the half's region, so
         // the walk that adds them reads 16 contiguous bytes per value quadruple (the totals
         // launch has the walk's work split, so both see the same order)
-        auto seg_total = [&](int t) -> float* { return sg.tot + (bh * (sg.total - 1) + t) * kSegElems + half * (DK * DK); };
+        auto seg_total = [&](int t) -> float* { return sg.tot + (bh * sg.slots + t) * kSegElems + half * (DK * DK); };
         auto tot_at = [&](int rt, int ct) { return ((rt * NCT + ct) * kWideThreads + tid) * 4; };
         // inputs of the first three chunks (the walk keeps three chunks in flight)
         Regs R0, R1, R2;
@@ -754,6 +758,42 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
         run(std::integral_constant<int, DV>{});
 }
 
+// Final states from the totals of all segments, without a second walk:
+//
+//   X_end = sum_t c_t T_t,   c_t = D_{t+1} ... D_{S-1}.
+//
+// The totals are the split-product walk's (one part per workgroup), in its register order:
+// block (sequence, part, row tile rt, column tile ct of a wave) sums one 16-byte quadruple
+// per thread, so every load is a whole 1-KiB wave access.  Bound by HBM (S + 1 states moved
+// per sequence); the segments are few, so it is a few microseconds beside the walk.
+template <int DK, int DV>
+__global__ __launch_bounds__(kWideThreads) void segment_combine_kernel(StateArgs a, SegPlan sg)
+{
+    constexpr int NS = DK / 32, CS = kWideThreads / kWave / NS;
+    constexpr int NCH = DK / 16 / CS, NCG = DV / 16 / CS;  // column tiles of a wave: H, G
+    const int64_t bh = blockIdx.x / (2 * (NCH + NCG));
+    int q = int(blockIdx.x % (2 * (NCH + NCG)));
+    const int part = q >= 2 * NCH;
+    q -= part ? 2 * NCH : 0;
+    const int nct = part ? NCG : NCH, rt = q / nct, ct = q % nct;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const float* tot = sg.tot + bh * sg.slots * (int64_t(DK) * (DK + DV)) + part * (DK * DK) +
+                       (q * kWideThreads + tid) * 4;
+    f32x4 x = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    float c = 1.0f;
+    for (int t = sg.total - 1; t >= 0; --t) {
+        x += c * *reinterpret_cast<const f32x4*>(tot + t * (int64_t(DK) * (DK + DV)));
+        c *= sg.dec[bh * sg.total + t];
+    }
+    const int R = 32 * (wave % NS) + 16 * rt + 4 * (lane / 16), col = 16 * (wave / NS * nct + ct) + lane % 16;
+    if (part) {
+        if (a.final_G) *reinterpret_cast<f32x4*>(a.final_G + bh * (int64_t(DV) * DK) + col * DK + R) = x;
+    } else if (a.final_H) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a.final_H[bh * (int64_t(DK) * DK) + (R + e) * DK + col] = x[e];
+    }
+}
+
 // Segments of the wide scan for bh sequences of n_chunks chunks: doubled while the
 // (sequence, part, segment) workgroups still fit the compute units once (the kernel's
 // LDS allows one workgroup per unit) and each segment keeps at least kMinSegChunks
@@ -765,6 +805,28 @@ int wide_segments(int64_t bh, int n_chunks)
     int S = 1;
     while (2 * bh * (2 * S) <= kComputeUnits && n_chunks / (2 * S) >= kMinSegChunks) S *= 2;
     return S;
+}
+
+// Segments of a states-only scan, whose segments all run side by side in one launch (no
+// second walk: their totals are the result but for the combination).  The launch takes
+// ceil(workgroups / compute units) rounds of len chunks; S minimises that, with the
+// combination counted as kCombineChunks chunks of walk (~2 us each) when there is one, and a
+// chunk's worth per 16 segments it reads.  A segment keeps at least two chunks, so that the
+// totals fit the half workspace a states-only call has.
+constexpr int kCombineChunks = 4;
+int final_segments(int64_t bh, int n_chunks)
+{
+    int best = 1;
+    int64_t cost = int64_t(n_chunks) * ((2 * bh + kComputeUnits - 1) / kComputeUnits);
+    for (int S = 2; S <= 128 && n_chunks / S >= 2; ++S) {
+        const int len = (n_chunks + S - 1) / S;
+        const int64_t c = int64_t(len) * ((2 * bh * S + kComputeUnits - 1) / kComputeUnits) + kCombineChunks + S / 16;
+        if (c < cost) {
+            cost = c;
+            best = S;
+        }
+    }
+    return best;
 }
 
 template <int DK, int DV, bool STORE, bool SPLIT, bool PLAIN = false, bool X3 = false>
@@ -780,16 +842,27 @@ hipError_t launch_wide(const StateArgs& a, hipStream_t stream)
     const int64_t bh = a.s.batch * a.s.heads;
     const int nc = a.s.n_chunks;
     const bool fin = a.final_H != nullptr || a.final_G != nullptr;
-    int S = wide_segments(bh, nc);
+    const bool final_only = !a.store_chunks;
+    int S = final_only ? final_segments(bh, nc) : wide_segments(bh, nc);
     int len = (nc + S - 1) / S;
     S = (nc + len - 1) / len;
-    const int64_t tot_elems = bh * (S - 1) * int64_t(DK) * (DK + DV);
+    const int slots = final_only ? S : S - 1;
+    const int64_t tot_elems = bh * slots * int64_t(DK) * (DK + DV);
     const size_t need = size_t(tot_elems + bh * S) * sizeof(float);
     if (S > 1 && (a.seg_ws == nullptr || a.seg_bytes < need)) {
         S = 1;
         len = nc;
     }
-    SegPlan sg{len, S, 0, S, false, a.seg_ws, S > 1 ? a.seg_ws + tot_elems : nullptr};
+    SegPlan sg{len, S, 0, S, false, slots, a.seg_ws, S > 1 ? a.seg_ws + tot_elems : nullptr};
+    if (S > 1 && final_only) {
+        sg.totals = true;
+        launch_wide_kernel<DK, DV, false, true>(a, sg, bh, stream);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        constexpr int kTiles = 2 * (DK + DV) / 16 / (kWideThreads / kWave / (DK / 32));  // row x column tiles of a wave, both parts
+        hipLaunchKernelGGL((segment_combine_kernel<DK, DV>), dim3(unsigned(bh * kTiles)), dim3(kWideThreads), 0, stream, a, sg);
+        return hipGetLastError();
+    }
     if (S > 1) {
         // segment totals T_0 .. T_{S-2} (the last one is never needed); fp32-accurate
         // (split products) when fp32 final states come out
@@ -806,11 +879,6 @@ hipError_t launch_wide(const StateArgs& a, hipStream_t stream)
             launch_wide_kernel<DK, DV, false, true>(a, p1, bh, stream);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-    }
-    if (!a.store_chunks) {
-        // final states only: the last segment's walk alone produces them
-        sg.first = S - 1;
-        sg.count = 1;
     }
     if (a.store_chunks && a.x3)  // fp32 H_c fragments, G_c high and low planes, fp32-accurate
         launch_wide_kernel<DK, DV, true, true, false, true>(a, sg, bh, stream);

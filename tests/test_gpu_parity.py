@@ -259,6 +259,30 @@ def test_segmented_state_scan_matches_oracle(dk, dv):
     assert rel_l2(Gs.cpu().numpy(), G1.cpu().numpy()) <= 1e-6
 
 
+@pytest.mark.parametrize("bh,T", [(1, 64), (1, 3 * 64 + 1), (1, 4 * 64), (2, 23 * 64 + 5), (3, 9 * 64 + 63), (70, 5 * 64 + 1),
+                                  (130, 4 * 64 + 2)])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_states_only_scan_combines_all_segments(bh, T, dk, dv):
+    """States-only call with scratch: every segment's total in one launch, then their
+    combination (one chunk up to many segments, ragged last segments, more sequences than
+    fit the compute units once).  Gates near one keep every segment visible, a zero gate
+    resets memory inside one; the scratch starts as NaN, so a total read before it is written
+    shows.  Final states against the oracle (split-product walk: ~2e-6) and the call without
+    scratch (one walk), 64-bit sums of at most T terms each rounded at 2^-17."""
+    x = W.forward_inputs(bh, 1, T, dk, dv, "bf16", 5.0, seed=T + dk + dv + bh)
+    x["gamma"][bh // 2, 0, T // 3] = 0.0
+    d = to_device(x, "bf16")
+    need = L.forward_workspace_bytes(bh, 1, T, dk, dv, 64)
+    ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    Hs, Gs = L.prefill_states(d["k"], d["v"], d["gamma"], d["beta"], workspace=ws)
+    H1, G1 = L.prefill_states(d["k"], d["v"], d["gamma"], d["beta"])
+    torch.cuda.synchronize()
+    ref = oracle.forward(x["q"], x["k"], x["v"], x["gamma"], x["beta"], x["lam"], 0, want_states=True)
+    assert rel_l2(Hs.cpu().numpy(), ref["H"]) <= 1e-5 and rel_l2(Gs.cpu().numpy(), ref["G"]) <= 1e-5
+    assert rel_l2(Hs.cpu().numpy(), H1.cpu().numpy()) <= 1e-6
+    assert rel_l2(Gs.cpu().numpy(), G1.cpu().numpy()) <= 1e-6
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_segmented_forward_bf16_states_only_path(d):
     """The forward without fp32 final states: the bf16 scan's segment totals and its
