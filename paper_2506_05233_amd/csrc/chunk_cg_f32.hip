@@ -557,7 +557,12 @@ hipError_t launch_mma(const CgArgs& a, hipStream_t stream)
 template <typename Tin, int DK>
 hipError_t launch_dk(const CgArgs& a, hipStream_t stream)
 {
-    if (a.s.chunk == 64) return launch_mma<Tin, DK>(a, stream);
+    if (a.s.chunk == 64) {
+        // d_k = 64: the six-term products on the bf16 matrix cores (the state's three parts fit
+        // the registers); at d_k = 128 they do not, and the fp32 matrix cores run it
+        if constexpr (DK == 64) return launch_chunk_cg_f32_split(a, stream);
+        else return launch_mma<Tin, DK>(a, stream);
+    }
     const unsigned blocks = unsigned(a.s.batch * a.s.heads * a.s.n_chunks);
     switch (a.s.chunk) {
         case 16: hipLaunchKernelGGL((chunk_cg_f32_kernel<Tin, DK, 16>), dim3(blocks), dim3(kThreads), 0, stream, a); break;

@@ -78,6 +78,8 @@ struct CgArgs {
     const float* rhs = nullptr;
 };
 hipError_t launch_chunk_cg_f32(const CgArgs& a, hipStream_t stream);
+// its chunk 64, d_k = 64 case (see chunk_cg_f32_split.hip)
+hipError_t launch_chunk_cg_f32_split(const CgArgs& a, hipStream_t stream);
 
 // Backward pass (fp32, chunk 64), in stages on one stream: 0 the right-hand sides
 // u_t = G_t^T e_t, 1 the reverse adjoint scan, 2 the per-chunk gradients, 3 the

@@ -683,3 +683,35 @@ def test_packed_decode_tolerance_counts():
     assert np.abs(got - rst).max() <= 1
     same = got == rst
     assert rel_l2(out.cpu().numpy()[same], ro[same]) <= TOL_F32
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dv", [64, 128])
+@pytest.mark.parametrize("T", [1, 15, 17, 33, 48, 63, 65, 64 + 16, 3 * 64 + 49])
+def test_f32_products_on_split_operands(dtype, dv, T):
+    """fp32 forward and solve at d_k = 64 (three bf16 parts per operand): lengths at the edges
+    of the 16-token sub-chunks and of the chunk, zero gates on a sub-chunk's first and last
+    token, a run of gates whose product underflows, beta = 0 and a zero query; q* and the
+    output against the oracle.  Each product term is exact to 2^-26, so the error is fp32
+    rounding: q* within 2e-6 of its norm (sums of up to 64 + 64 terms in 12 steps; measured
+    1e-7 to 4e-7).  o_t = G_t q*_t may cancel (a single token's k^T q* can be near zero), so
+    its error is bounded by 2e-6 of |G_t| |q*_t|, which a rounding of G_t or q*_t moves it by."""
+    x = W.forward_inputs(2, 3, T, 64, dv, dtype, 3.0, seed=900 + T + dv)
+    x["gamma"][0, 0, T // 2] = 0.0
+    x["gamma"][0, 1, 16 * (T // 32)] = 0.0
+    x["gamma"][0, 2, max(0, 16 * (T // 16) - 1)] = 0.0
+    x["gamma"][1, 0, T // 3:T // 3 + 20] = 1e-6
+    x["beta"][1, 1, ::3] = 0.0
+    x["q"][1, 2, T // 2] = 0.0
+    got = _gpu_forward(x, dtype, 12, 64, precision=L.MESA_PREC_F32, want_qstar=True)
+    ref = oracle.forward(x["q"], x["k"], x["v"], x["gamma"], x["beta"], x["lam"], 12, want_qstar=True)
+    for b in range(2):
+        for h in range(3):
+            G, scale = np.zeros((dv, 64)), 0.0
+            for t in range(T):
+                G = x["gamma"][b, h, t] * G + x["beta"][b, h, t] * np.outer(x["v"][b, h, t], x["k"][b, h, t])
+                scale += np.sum(G * G) * np.sum(ref["qstar"][b, h, t] ** 2)
+            e_out = np.linalg.norm(got["out"][b, h] - ref["out"][b, h])
+            e_q = np.linalg.norm(got["qstar"][b, h] - ref["qstar"][b, h])
+            assert e_out <= 2e-6 * np.sqrt(scale), (b, h, e_out, scale)
+            assert e_q <= 2e-6 * np.linalg.norm(ref["qstar"][b, h]), (b, h, e_q)

@@ -78,7 +78,7 @@ def reports():
 
 
 def test_every_source_reports_its_kernels(reports):
-    kinds = ["chunk_cg_bf16_kernel", "chunk_cg_x3_kernel", "chunk_cg_f32_mma_kernel", "chunk_state_wide_kernel",
+    kinds = ["chunk_cg_bf16_kernel", "chunk_cg_x3_kernel", "chunk_cg_f32_mma_kernel", "chunk_cg_f32_split_kernel", "chunk_state_wide_kernel",
              "decode_step_kernel", "bwd_grad_kernel", "bwd_adjoint_kernel", "bwd_rhs_kernel", "frontend_kernel",
              "output_norm_kernel"]
     for k in kinds:
