@@ -18,7 +18,7 @@
 //   3. G <- gamma G + beta v k^T and o = G x: thread c keeps column c of G,
 //      writes it back, and the row sums of G diag(x) are reduced across lanes
 //      and waves.
-// All arithmetic is fp32.
+// All arithmetic is fp32.  Few pairs take a kernel of their own (decode_few_kernel below).
 #include "mesa_device.hpp"
 #include "mesa_kernels.hpp"
 
@@ -249,10 +249,242 @@ void decode_step_kernel(DecodeArgs a)
     }
 }
 
+// Few pairs (see launch_dk): the step is then one chain of dependent products, and the kernel
+// is built for the length of that chain.  One workgroup of d_k / 16 waves per pair; wave w
+// holds rows 16 w .. 16 w + 15 of H (lane (g, n): row 16 w + n, columns 16 e + 4 g .. + 3) and a
+// share of G's rows alike, both on their way from the start; the updated states are stored
+// after the solve, since a barrier waits for the stores before it.  A product is 32
+// multiply-adds per lane (d_k = 128) and a sum over four lanes; its 16 rows of w go to LDS, and
+// after the one barrier of the iteration (the kernel above has three) every wave reads all of w
+// and runs the vector updates and both dot products of the whole vector itself (elements l and
+// l + 64 in lane l, the same arithmetic in every wave, so all waves hold the same scalars and
+// take the same branches), handing p to its own product through a private LDS copy.
+__device__ __forceinline__ float quotient(float a, float b)
+{
+    // a / b by the hardware reciprocal and one correction (within one ulp, without the range
+    // scaling of the full division: a and b are normal numbers here)
+    const float rc = __builtin_amdgcn_rcpf(b), q = a * rc;
+    return fmaf(fmaf(-q, b, a), rc, q);
+}
+
+template <typename Tin, int DK, int DV, bool PACKED>
+__global__ __launch_bounds__(DK * 4) void decode_few_kernel(DecodeArgs a)
+{
+    constexpr int NW = DK / 16;      // waves per pair
+    constexpr int NT = NW * kWave;   // threads
+    constexpr int EC = DK / 16;      // 4-column groups per lane of a row
+    constexpr int EV = DK / kWave;   // vector elements per lane
+    constexpr int GT = (DV / 16 + NW - 1) / NW;  // 16-row tiles of G per wave
+    constexpr int NH = PACKED ? DK / 2 + 1 : DK;
+    constexpr int HALF = DK / 2;
+    const int64_t pair = blockIdx.x;
+    const int h = int(blockIdx.x % unsigned(a.heads));
+    const int tid = threadIdx.x;
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave, g = lane / 16, n = lane % 16;
+    const int row = 16 * wv + n;     // this lane's row of H
+
+    __shared__ __attribute__((aligned(16))) float sk[DK], sv[DV];
+    __shared__ __attribute__((aligned(16))) float sp[NW][DK];   // each wave's copy of its product's vector
+    __shared__ float sw[2][DK];
+    __shared__ __attribute__((aligned(16))) float sh[PACKED ? NH * DK : 4];  // the updated diagonals
+
+    float* Hp = a.H + pair * NH * DK;
+    float* Gp = a.G + pair * int64_t(DV) * DK;
+    constexpr int NP = PACKED ? (NH * DK / 4 + NT - 1) / NT : 1;  // packed: 16-byte pieces per thread
+    f32x4 hr[EC], hp[NP], gr[GT][EC];
+    const Tin* kp = static_cast<const Tin*>(a.k) + pair * DK;
+    const Tin* vp = static_cast<const Tin*>(a.v) + pair * DV;
+    const Tin* qp = static_cast<const Tin*>(a.q) + pair * DK;
+    const float kt = tid < DK ? to_f32(kp[tid]) : 0.0f, vt = tid < DV ? to_f32(vp[tid]) : 0.0f;
+    const float gam = a.gamma[pair], bet = a.beta[pair];
+    if constexpr (!PACKED) {
+#pragma unroll
+        for (int e = 0; e < EC; ++e) hr[e] = *reinterpret_cast<const f32x4*>(Hp + row * DK + 16 * e + 4 * g);
+    } else {
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            if (tid + u * NT < NH * DK / 4) hp[u] = *reinterpret_cast<const f32x4*>(Hp + 4 * (tid + u * NT));
+    }
+    float q[EV], lam[EV];
+#pragma unroll
+    for (int u = 0; u < EV; ++u) {
+        q[u] = to_f32(qp[lane + kWave * u]);
+        lam[u] = a.lambda[int64_t(h) * DK + lane + kWave * u];
+    }
+#pragma unroll
+    for (int t = 0; t < GT; ++t)
+        if (16 * (wv + t * NW) < DV)
+#pragma unroll
+            for (int e = 0; e < EC; ++e)
+                gr[t][e] = *reinterpret_cast<const f32x4*>(Gp + (16 * (wv + t * NW) + n) * DK + 16 * e + 4 * g);
+    if (tid < DK) sk[tid] = kt;
+    if (tid < DV) sv[tid] = vt;
+    __syncthreads();
+
+    // ---- H <- gamma H + beta k k^T, each element with the operation order of the kernel above
+    // (element (i, j) takes (beta k_j) k_i; on the packed diagonals (beta k_i) k_{i+k})
+    if constexpr (!PACKED) {
+        const float kr = sk[row];
+#pragma unroll
+        for (int e = 0; e < EC; ++e) {
+            const f32x4 kc = *reinterpret_cast<const f32x4*>(sk + 16 * e + 4 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) hr[e][i] = gam * hr[e][i] + bet * kc[i] * kr;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const int o = 4 * (tid + u * NT);
+            if (o >= NH * DK) continue;
+            const int k = o / DK, i0 = o % DK;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) hp[u][i] = gam * hp[u][i] + bet * sk[i0 + i] * sk[(i0 + i + k) % DK];
+            *reinterpret_cast<f32x4*>(sh + o) = hp[u];
+        }
+        __syncthreads();
+        // H[R][c]: diagonal (c - R) mod d_k from R, or (R - c) mod d_k from c; on the last
+        // diagonal the entry at the smaller index mod d_k / 2
+#pragma unroll
+        for (int e = 0; e < EC; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = 16 * e + 4 * g + i, d = (c - row) & (DK - 1);
+                hr[e][i] = sh[d < HALF ? d * DK + row : d == HALF ? d * DK + row % HALF : (DK - d) * DK + c];
+            }
+    }
+    // diagonal of H + Lambda for this lane's vector elements (in tile wv of its row, where
+    // column 16 wv + 4 g + i is the row: 4 g + i = n)
+    float* const pv = sp[wv];
+#pragma unroll
+    for (int e = 0; e < EC; ++e)
+        if (e == wv) {
+            const int i = n - 4 * g;
+            if (i >= 0 && i < 4) sw[1][row] = i == 0 ? hr[e][0] : i == 1 ? hr[e][1] : i == 2 ? hr[e][2] : hr[e][3];
+        }
+    __syncthreads();
+    float dg[EV];
+#pragma unroll
+    for (int u = 0; u < EV; ++u) dg[u] = sw[1][lane + kWave * u] + lam[u];
+
+    // this lane's part of a row times the vector in pv, summed over the row's four lanes
+    auto row_dot = [&](const f32x4 (&m)[EC]) __attribute__((always_inline)) -> float {
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int e = 0; e < EC; ++e) acc += m[e] * *reinterpret_cast<const f32x4*>(pv + 16 * e + 4 * g);
+        return row_pair_sums((acc[0] + acc[1]) + (acc[2] + acc[3]));
+    };
+    auto to_wave = [&](const float (&v)[EV]) __attribute__((always_inline)) {  // a wave's LDS accesses complete in order
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < EV; ++u) pv[lane + kWave * u] = v[u];
+        __builtin_amdgcn_wave_barrier();
+    };
+    // w = (H + Lambda) v; the two buffers alternate, so one is rewritten only after every
+    // wave has passed the barrier in between
+    int slot = 0;
+    auto gemv = [&](const float (&v)[EV], float (&w)[EV]) __attribute__((always_inline)) {
+        to_wave(v);
+        const float y = row_dot(hr);
+        if (g == 0) sw[slot][row] = y;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < EV; ++u) w[u] = sw[slot][lane + kWave * u] + lam[u] * v[u];
+        slot ^= 1;
+    };
+    auto dot = [&](const float (&u)[EV], const float (&v)[EV]) __attribute__((always_inline)) -> float {
+        float s = u[0] * v[0];
+#pragma unroll
+        for (int i = 1; i < EV; ++i) s += u[i] * v[i];
+        return wave_sum(s);
+    };
+
+    // ---- CG (Alg. 1) on the whole vector in every wave, for q 2^-qsh (|q 2^-qsh|^2 in [1/2, 2))
+    const int qsh = cg_scale_shift(dot(q, q));
+    float x[EV], r[EV], p[EV], w[EV];
+#pragma unroll
+    for (int u = 0; u < EV; ++u) {
+        q[u] *= __builtin_ldexpf(1.0f, -qsh);
+        x[u] = q[u] / dg[u];
+    }
+    gemv(x, w);
+#pragma unroll
+    for (int u = 0; u < EV; ++u) p[u] = r[u] = q[u] - w[u];
+    float delta = dot(r, r);
+    const float thr = a.eps2 * delta;  // Alg. 1: stop once |r|^2 <= eps^2 |r_0|^2
+    int steps = 0;                     // iterations that updated x
+    if (delta >= kMinNormal) {
+        for (int it = 0; it < a.n_cg; ++it) {
+            gemv(p, w);
+            const float pw = dot(p, w);
+            if (!(pw >= kMinNormal)) break;
+            const float alpha = quotient(delta, pw);
+#pragma unroll
+            for (int u = 0; u < EV; ++u) {
+                x[u] += alpha * p[u];
+                r[u] -= alpha * w[u];
+            }
+            ++steps;
+            const float dn = dot(r, r);
+            if (dn <= thr || !(dn >= kMinNormal)) break;
+            const float bcg = quotient(dn, delta);
+#pragma unroll
+            for (int u = 0; u < EV; ++u) p[u] = r[u] + bcg * p[u];
+            delta = dn;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < EV; ++u) x[u] *= __builtin_ldexpf(1.0f, qsh);
+    if (a.steps && tid == 0) a.steps[pair] = steps;
+    if constexpr (!PACKED) {
+#pragma unroll
+        for (int e = 0; e < EC; ++e) *reinterpret_cast<f32x4*>(Hp + row * DK + 16 * e + 4 * g) = hr[e];
+    } else {
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const int o = 4 * (tid + u * NT);
+            if (o < HALF * DK + HALF) *reinterpret_cast<f32x4*>(Hp + o) = hp[u];  // the last diagonal's second half is not stored
+        }
+    }
+
+    // ---- G <- gamma G + beta v k^T and o = G x (no wave needs another's rows)
+    to_wave(x);
+#pragma unroll
+    for (int t = 0; t < GT; ++t) {
+        const int r0 = 16 * (wv + t * NW);
+        if (r0 >= DV) continue;
+        const float ve = sv[r0 + n];
+#pragma unroll
+        for (int e = 0; e < EC; ++e) {
+            const f32x4 kc = *reinterpret_cast<const f32x4*>(sk + 16 * e + 4 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) gr[t][e][i] = gam * gr[t][e][i] + bet * kc[i] * ve;
+            *reinterpret_cast<f32x4*>(Gp + (r0 + n) * DK + 16 * e + 4 * g) = gr[t][e];
+        }
+        const float o = row_dot(gr[t]);
+        if (g == 0) a.out[pair * DV + r0 + n] = o;
+    }
+}
+
+constexpr int64_t kFewElems = 512 * 128;  // pairs x d_k up to which the few-pairs kernel runs
+
 template <typename Tin, int DK, bool PACKED>
 hipError_t launch_dk(const DecodeArgs& a, hipStream_t stream)
 {
     const unsigned blocks = unsigned(a.batch * a.heads);
+    // Up to two workgroups of the few-pairs kernel per compute unit at d_k = 128 (four at
+    // 64) its shorter chain wins, beyond that the kernel above, which keeps more pairs in flight
+    // (us per step, 15 CG steps, few-pairs kernel against the one above; packed in brackets):
+    //   d 128: 48 pairs 19.3 / 25.4 (18.9 / 27.3), 512 32.0 / 37.2 (31.6 / 37.9), 768 48.9 / 44.0
+    //   d 64: 48 pairs 11.6 / 15.0 (11.9 / 16.5), 1024 21.2 / 21.5 (21.3 / 21.9), 2048 32.6 / 29.7
+    // It moves the states in 16-byte pieces; states aligned to less take the kernel above.
+    const bool aligned = uintptr_t(a.H) % 16 == 0 && uintptr_t(a.G) % 16 == 0;
+    if (aligned && int64_t(blocks) * DK <= kFewElems) {
+        if (a.d_v == 64)
+            hipLaunchKernelGGL((decode_few_kernel<Tin, DK, 64, PACKED>), dim3(blocks), dim3(DK * 4), 0, stream, a);
+        else
+            hipLaunchKernelGGL((decode_few_kernel<Tin, DK, 128, PACKED>), dim3(blocks), dim3(DK * 4), 0, stream, a);
+        return hipGetLastError();
+    }
     if (a.d_v == 64)
         hipLaunchKernelGGL((decode_step_kernel<Tin, DK, 64, PACKED>), dim3(blocks), dim3(DK), 0, stream, a);
     else

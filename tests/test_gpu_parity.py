@@ -715,3 +715,62 @@ def test_f32_products_on_split_operands(dtype, dv, T):
             e_q = np.linalg.norm(got["qstar"][b, h] - ref["qstar"][b, h])
             assert e_out <= 2e-6 * np.sqrt(scale), (b, h, e_out, scale)
             assert e_q <= 2e-6 * np.linalg.norm(ref["qstar"][b, h]), (b, h, e_q)
+
+
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_decode_few_pairs_matches_many_pairs_kernel(dk, dv, packed):
+    """The largest step of the few-pairs kernel (pairs x d_k = 65536), the next larger one, and
+    states that are only 4-byte aligned (which take the many-pairs kernel) on the same pairs:
+    the states agree bit for bit (one operation order for every element), the outputs to fp32
+    rounding of a 12-step solve, and the iteration counts under a tolerance nearly always."""
+    n = 65536 // dk
+    g = torch.Generator(device="cuda").manual_seed(dk + dv)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    def unit(*shape):
+        x = normal(*shape)
+        return x / x.norm(dim=-1, keepdim=True)
+
+    q, k, v = unit(n + 1, 1, dk), unit(n + 1, 1, dk), normal(n + 1, 1, dv)
+    gam, bet = torch.sigmoid(normal(n + 1, 1) + 4), torch.sigmoid(normal(n + 1, 1))
+    lam = torch.rand((1, dk), generator=g, device="cuda") * 0.75 + 0.25
+    q[3] = 0.0
+    gam[5] = 0.0
+    bet[7] = 0.0
+    ks = unit(n + 1, 1, 40, dk)
+    H = torch.matmul(ks.transpose(-1, -2).contiguous(), ks)
+    H = 0.5 * (H + H.transpose(-1, -2)).contiguous()
+    G = normal(n + 1, 1, dv, dk)
+    if packed:
+        H = L.pack_state(H)
+        H[:, :, dk // 2, dk // 2:] = 0.0  # not stored by a step
+
+    def step(m, eps, misaligned=False):
+        def place(t):
+            t = t[:m].contiguous()
+            if not misaligned:
+                return t.clone()
+            buf = torch.empty(t.numel() + 1, dtype=torch.float32, device="cuda")
+            view = buf[1:].view(t.shape)
+            view.copy_(t)
+            return view
+        h, gg = place(H), place(G)
+        steps = torch.empty((m, 1), dtype=torch.int32, device="cuda")
+        out = L.decode_step(h, gg, q[:m].contiguous(), k[:m].contiguous(), v[:m].contiguous(), gam[:m].contiguous(),
+                            bet[:m].contiguous(), lam, 12, eps=eps, steps_out=steps, packed=packed)
+        torch.cuda.synchronize()
+        return out, h, gg, steps
+
+    for eps in (0.0, 1e-3):
+        few = step(n, eps)
+        for other in (step(n + 1, eps), step(n, eps, misaligned=True)):
+            assert torch.equal(few[1], other[1][:n]) and torch.equal(few[2], other[2][:n])
+            diff = few[3] != other[3][:n]
+            assert float(diff.float().mean()) <= 0.01
+            same = ~diff[:, 0]
+            e = (few[0][same] - other[0][:n][same]).norm() / other[0][:n][same].norm()
+            assert float(e) <= 2e-6
+        assert not few[0][3].any()
