@@ -574,6 +574,9 @@ struct AdjSeg {
     bool totals;  // write T_s and D_s instead of the per-chunk adjoints
     float* tot;   // [B*H, total, d_k (d_k + d_v)]: T_s of S^H then of A^G (chunk layout)
     float* dec;   // [B*H, total]: D_s
+    // with totals, segments of one chunk each: T_n goes straight to the place of the adjoint
+    // that chunk n passes on, chunk n - 1's, for bwd_adjoint_scan_kernel to complete
+    bool direct;
 };
 
 template <int DK, int DV, bool SPLIT>
@@ -926,7 +929,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_adjoint_kernel(BwdArgs a, Adj
         }
     }
     if (sg.totals) {
-        float* tb = seg_tile(seg);
+        float* tb = sg.direct ? out + ((bh * nc + seg - 1) * nrow + r0 + 16 * w + 4 * g) * int64_t(DK) + ln : seg_tile(seg);
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
@@ -1372,6 +1375,45 @@ __global__ __launch_bounds__(kGradThreads) void bwd_grad_kernel(BwdArgs a)
     }
 }
 
+// Completes the adjoints in place from the chunks' own totals (few, short sequences):
+//
+//   X_{nc-1} = 0,   X_n = T_{n+1} + D_{n+1} X_{n+1}   (T_{n+1} stands at X_n).
+//
+// One thread per four elements walks the chunks; kScanAhead loads are in flight, so the walk
+// costs its bytes (the adjoints read and written once) and not a memory round trip per chunk.
+constexpr int kScanAhead = 8;
+__global__ __launch_bounds__(kThreads) void bwd_adjoint_scan_kernel(BwdArgs a, const float* dec)
+{
+    const int nc = a.s.n_chunks;
+    const int nH = a.s.d_k * a.s.d_k / 4, nG = a.s.d_v * a.s.d_k / 4, per = nH + nG;  // 16-byte pieces of a chunk
+    const int64_t e = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    const int64_t bh = e / per;
+    if (bh >= a.s.batch * a.s.heads) return;
+    const int q = int(e % per);
+    const bool isG = q >= nH;
+    const int64_t stride = isG ? nG : nH;
+    f32x4* p = reinterpret_cast<f32x4*>(isG ? a.AG : a.SH) + bh * nc * stride + (isG ? q - nH : q);
+    const float* d = dec + bh * nc;
+    f32x4 x = kZero4;
+    p[(nc - 1) * stride] = x;
+    for (int n = nc - 2; n >= 0; n -= kScanAhead) {
+        f32x4 t[kScanAhead];
+        float dn[kScanAhead];
+#pragma unroll
+        for (int u = 0; u < kScanAhead; ++u) {
+            const int m = n - u > 0 ? n - u : 0;
+            t[u] = p[m * stride];
+            dn[u] = d[m + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kScanAhead; ++u)
+            if (n - u >= 0) {
+                x = t[u] + dn[u] * x;
+                p[(n - u) * stride] = x;
+            }
+    }
+}
+
 // ---------------------------------------------------------------- dLambda
 // dLambda[h][b] = sum over the batch and the chunks of the per-chunk partial sums:
 // one workgroup per head; thread (b, slot) sums every kThreads / d_k-th (batch, chunk)
@@ -1429,7 +1471,27 @@ hipError_t launch_bwd_dims(const BwdArgs& a, hipStream_t stream, int stage)
             while (bh * NTILE * (2 * S) <= 256 && nc / (2 * S) >= 8) S *= 2;
             const int len = (nc + S - 1) / S;
             S = (nc + len - 1) / len;
-            AdjSeg sg{len, S, 0, S, false, a.u, a.u + bh * S * int64_t(DK) * (DK + DV)};
+            // The walk is a chain of chunk steps of ~4.5 us, which few sequences leave most of the
+            // chip idle under; the chunks' totals side by side and a scan over them need only
+            // the rounds of the totals, but move the adjoints twice more (~2.7 MB per us) and
+            // cost a launch.  One step of walk saved is worth 12 MB, the launch 11 MB (backward,
+            // walk / scan: 8 sequences of 13 chunks d 64 fp32 128 / 86 us, 16 of 64 d 128 bf16
+            // 558 / 495, 16 of 256 2124 / 1812; not 64 of 16: 464 / 480, 128 of 5: 282 / 305).
+            const int64_t bytes = bh * nc * int64_t(DK) * (DK + DV) * 4;
+            const int64_t resident = 512;  // workgroups the chip holds at once
+            const int64_t walk = (S > 1 ? 2 * len : nc) * ((bh * NTILE * S + resident - 1) / resident);
+            const int64_t rounds = (bh * NTILE * (nc - 1) + resident - 1) / resident;
+            if (nc > 1 && bytes + 11000000 < (walk - rounds) * 12000000) {
+                AdjSeg p1{1, nc, 1, nc - 1, true, nullptr, a.u, true};
+                hipLaunchKernelGGL((bwd_adjoint_kernel<DK, DV, kSplit>), dim3(unsigned(bh * NTILE * (nc - 1))), dim3(kThreads), 0,
+                                   stream, a, p1);
+                const hipError_t e = hipGetLastError();
+                if (e != hipSuccess) return e;
+                hipLaunchKernelGGL(bwd_adjoint_scan_kernel, dim3(unsigned((bytes / 16 / nc + kThreads - 1) / kThreads)),
+                                   dim3(kThreads), 0, stream, a, a.u);
+                break;
+            }
+            AdjSeg sg{len, S, 0, S, false, a.u, a.u + bh * S * int64_t(DK) * (DK + DV), false};
             if (S > 1) {
                 AdjSeg p1 = sg;
                 p1.first = 1;

@@ -189,3 +189,26 @@ def test_backward_segmented_walks_long_memory(precision, tol):
     _say("segmented backward: %s" % "  ".join("%s %.2e" % kv for kv in errs.items()))
     for k, e in errs.items():
         assert e <= tol, (k, e)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("bh,T", [(1, 129), (2, 13 * 64 + 7), (1, 35 * 64)])
+def test_adjoints_from_totals_and_scan(bh, T, dk, dv, dtype):
+    """Few, short sequences: the chunks' adjoint totals side by side and a scan over them (two
+    chunks up to more than the scan keeps in flight), and on the bf16 route the forward states
+    likewise.  Gates near one carry every later chunk's adjoint to the first, a zero gate cuts
+    one; the workspace starts as NaN.  Every gradient against the oracle."""
+    x = W.forward_inputs(1, bh, T, dk, dv, dtype, 5.0, seed=T + dk + dv)
+    x["gamma"][...] = np.maximum(x["gamma"], 0.99).astype(np.float32)
+    x["gamma"][0, bh - 1, T // 3] = 0.0
+    d = to_device(x, dtype)
+    dout = np.random.default_rng(T).standard_normal((1, bh, T, dv)).astype(np.float32)
+    ref = oracle.backward(x["q"], x["k"], x["v"], x["gamma"], x["beta"], x["lam"], dout, 10, want_solves=True)
+    ws = torch.full((L.backward_workspace_bytes(1, bh, T, dk, dv) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    g = L.backward(d["k"], d["v"], d["gamma"], d["beta"], d["lam"], torch.from_numpy(ref["qstar"].astype(np.float32)).cuda(),
+                   torch.from_numpy(dout).cuda(), 10, workspace=ws)
+    torch.cuda.synchronize()
+    tol = 2e-2 if dtype == "bf16" else 1e-5
+    for name in ("dq", "dk", "dv", "dgamma", "dbeta", "dlam"):
+        assert rel_l2(g[name].cpu().numpy(), ref[name]) <= tol, name
