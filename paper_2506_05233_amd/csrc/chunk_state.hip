@@ -266,7 +266,9 @@ __global__ __launch_bounds__(kThreads) void chunk_state_mfma_kernel(StateArgs a)
 // reads k-slot g = tokens 4j + g of the staged slices.
 constexpr int kF32Depth = 4;
 
-template <int DK, bool STORE>
+// MODE 0: final states only, 1: chunk states too, 2: one chunk's own total per workgroup, to
+// the place of the next chunk's state (for chunk_scan_kernel)
+template <int DK, int MODE>
 __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
 {
     constexpr int C = 64;
@@ -275,9 +277,11 @@ __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
     const int dv = s.d_v;
     const int nrt = (DK + dv) / 16;
     const int blk = xcd_major_block(blockIdx.x, gridDim.x);
+    constexpr bool STORE = MODE == 1;
     const int grp = blk % kGroups;
     const int rt = (blk / kGroups) % nrt;
-    const int64_t bh = blk / (kGroups * nrt);
+    const int unit = blk / (kGroups * nrt);  // the sequence, or (MODE 2) its chunk
+    const int64_t bh = MODE == 2 ? unit / (s.n_chunks - 1) : unit;
     const bool isG = rt * 16 >= DK;
     const int xr0 = isG ? rt * 16 - DK : rt * 16;  // first row of the tile within H or G
     const int nX = isG ? dv : DK;                  // rows of that state = width of its source
@@ -321,7 +325,7 @@ __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
 
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     const int64_t tile_off = (xr0 + 4 * g) * int64_t(DK) + c0 + m;  // element (4g, m) of the tile
-    float* chunk_dst = STORE ? static_cast<float*>(isG ? a.Gs : a.Hs) + bh * s.n_chunks * nX * int64_t(DK) + tile_off
+    float* chunk_dst = MODE != 0 ? static_cast<float*>(isG ? a.Gs : a.Hs) + bh * s.n_chunks * nX * int64_t(DK) + tile_off
                                       : nullptr;
     auto step = [&](int n, const Regs& R) {
         // gate scan (lane i = in-chunk token i; absent tokens have gamma 1, beta 0)
@@ -361,6 +365,16 @@ __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
     // bounds and unused), so the count of loads in flight is the same at every
     // point of every pass and each wait covers exactly the chunk it needs.
     static_assert(kF32Depth == 4, "the ring below holds four chunks");
+    if constexpr (MODE == 2) {
+        const int n = unit % (s.n_chunks - 1);
+        Regs R;
+        load(n, R);
+        step(n, R);
+        float* dst = chunk_dst + int64_t(n + 1) * nX * DK;
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii) dst[ii * DK] = acc[ii];
+        return;
+    }
     Regs R0, R1, R2, R3;
     const int nc = s.n_chunks;
     if (nc > 0) {
@@ -445,7 +459,17 @@ struct SegPlan {
     int slots;    // segment totals kept per sequence: total - 1, or total when all are combined
     float* tot;   // [B*H, slots, d_k (d_k + d_v)]: T_s of H, then of G (register order, see seg_total)
     float* dec;   // [B*H, total]: D_s
+    // with totals, segments of one chunk each: T_n goes straight to the place of the state that
+    // enters chunk n + 1, for chunk_scan_kernel to complete (its modes; 0 otherwise)
+    int direct;
+    int64_t part2;  // bytes from a bf16 fragment to the second half of its total's values
 };
+
+// Completion of chunk states from the chunks' own totals: layouts.
+constexpr int kScanPlain = 1;  // fp32 plain
+constexpr int kScanX3 = 2;     // fp32 H fragments, bf16 G high and low planes
+constexpr int kScanFrag = 3;   // bf16 fragments
+constexpr int kScanBoth = 4;   // bf16 fragments and fp32 plain (the totals stand in the latter)
 
 template <int DK, int DV, bool STORE, bool SPLIT, bool PLAIN = false, bool X3 = false>
 __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArgs a, SegPlan sg)
@@ -732,7 +756,30 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
         // fp32 output: the segment total and its decay, or, after the last segment, the
         // final states
         float* dst = nullptr;
-        if (sg.totals) {
+        if (sg.totals && sg.direct) {
+            const int64_t at = (bh * s.n_chunks + seg + 1) * int64_t(kStateElems);
+            if (sg.direct == kScanBoth) {
+                float* base = plain_base + at;
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+                        for (int ii = 0; ii < 4; ++ii) base[tile_off(rt, ct, ii)] = acc[rt][ct][ii];
+            } else {
+                // eight values of a fragment's lane: 16 bytes in its own place and 16 bytes in a
+                // second one (H of the split-operand layout: the fragment's two fp32 halves)
+                const bool fp32 = sg.direct == kScanX3 && part == 0;
+                char* base = fp32 ? reinterpret_cast<char*>(static_cast<float*>(a.Hs) + at) : reinterpret_cast<char*>(frag_base + at);
+                const int64_t step = fp32 ? 2 * kWave * 16 : kWave * 16, second = fp32 ? kWave * 16 : sg.part2;
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    char* q = base + ((ct0 + ct) * NS + sblk) * step + lane * 16;
+                    *reinterpret_cast<f32x4*>(q) = acc[0][ct];
+                    *reinterpret_cast<f32x4*>(q + second) = acc[1][ct];
+                }
+            }
+        } else if (sg.totals) {
             float* tb = seg_total(seg);
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt)
@@ -794,6 +841,155 @@ __global__ __launch_bounds__(kWideThreads) void segment_combine_kernel(StateArgs
     }
 }
 
+// Product over all 64 lanes of a wave; every lane receives it.
+__device__ __forceinline__ float wave_prod(float x)
+{
+    x *= dpp_f32<kDppQuadSwap1>(x, x);
+    x *= dpp_f32<kDppQuadSwap2>(x, x);
+    x *= dpp_f32<kDppRowRor4>(x, x);
+    x *= dpp_f32<kDppRowRor8>(x, x);
+    const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(s16[0]) * __uint_as_float(s16[1]);
+    const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(s32[0]) * __uint_as_float(s32[1]);
+}
+
+// Completes the chunk states in place from the chunks' own totals (few, short sequences):
+//
+//   X_0 = 0,   X_{n+1} = D_n X_n + T_n   (T_n stands at X_{n+1}), D_n the chunk's decay.
+//
+// One thread per eight elements (a fragment's lane; plain layout: per four) walks the chunks
+// with kAhead chunks' loads in flight, so the walk costs its bytes and not a memory round trip
+// per chunk.  Every workgroup forms the sequence's decays from the gates itself.
+constexpr int kScanChunks = 1024;  // longest sequence (its decays are kept in LDS)
+
+template <int MODE>
+__global__ __launch_bounds__(kThreads) void chunk_scan_kernel(StateArgs a, int64_t part2)
+{
+    const ForwardShape s = a.s;
+    const int nc = s.n_chunks, dk = s.d_k;
+    constexpr int E = MODE == kScanPlain ? 4 : 8;
+    const int nH = dk * dk / E, per = nH + s.d_v * dk / E;  // threads per sequence (a multiple of kThreads)
+    const int64_t bh = blockIdx.x / (per / kThreads);
+    const int e = int(blockIdx.x % (per / kThreads)) * kThreads + threadIdx.x;
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const bool isG = e >= nH;      // uniform: nH is a multiple of kThreads
+    const int q = isG ? e - nH : e;
+    const int64_t elems = int64_t(isG ? s.d_v : dk) * dk;  // of one chunk state of this part
+
+    __shared__ float sD[kScanChunks];
+    constexpr int NV = E / 4;
+    constexpr int kAhead = MODE == kScanBoth ? 8 : 16;  // chunks in flight
+    f32x4 t[kAhead][NV];
+    // addresses of this thread's values: 16-byte pieces at p0, p0 + d1 of a chunk
+    char* p0;
+    int64_t d1 = 0, stride;       // bytes
+    int plain[2] = {0, 0};        // kScanBoth: element offsets of the two quadruples in the plain state
+    float* pl = nullptr;
+    if (MODE == kScanPlain) {
+        p0 = static_cast<char*>(isG ? a.Gs : a.Hs) + bh * nc * elems * 4 + q * 16;
+        stride = elems * 4;
+    } else if (MODE == kScanX3 && !isG) {
+        p0 = static_cast<char*>(a.Hs) + bh * nc * elems * 4 + (int64_t(q / kWave) * 2 * kWave + q % kWave) * 16;
+        d1 = kWave * 16;
+        stride = elems * 4;
+    } else {
+        p0 = static_cast<char*>(isG ? a.Gs : a.Hs) + bh * nc * elems * 2 + int64_t(q) * 16;
+        d1 = part2;
+        stride = elems * 2;
+    }
+    if (MODE == kScanBoth) {
+        // fragment (t, sb), lane (g, m): X[16 t + m][32 sb + 16 h + 4 g ..]; the plain H holds the
+        // values of column 16 t + m from row 32 sb + 16 h + 4 g on (the same numbers: the tiles are
+        // [key feature][column]), the plain G its row
+        const int f = q / kWave, ns = dk / 32, tl = f / ns, sb = f % ns;
+        for (int h = 0; h < 2; ++h) {
+            const int R = 32 * sb + 16 * h + 4 * (lane / 16), c = 16 * tl + lane % 16;
+            plain[h] = isG ? c * dk + R : R * dk + c;
+        }
+        pl = (isG ? a.Gs32 : a.Hs32) + bh * nc * elems;
+    }
+    auto load = [&](int n, f32x4 (&v)[NV]) {
+        if constexpr (MODE == kScanBoth) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float* src = pl + n * elems + plain[h];
+                if (isG) v[h] = *reinterpret_cast<const f32x4*>(src);
+                else
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[h][i] = src[i * dk];
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < NV; ++h) v[h] = *reinterpret_cast<const f32x4*>(p0 + n * stride + h * d1);
+        }
+    };
+    auto store = [&](int n, const f32x4 (&x)[NV]) {
+        char* p = p0 + n * stride;
+        if constexpr (MODE == kScanPlain) {
+            *reinterpret_cast<f32x4*>(p) = x[0];
+        } else if (MODE == kScanX3 && !isG) {
+            *reinterpret_cast<f32x4*>(p) = x[0];
+            *reinterpret_cast<f32x4*>(p + d1) = x[1];
+        } else {
+            bf16x8 hi, lo;
+            split8(x[0], x[1], hi, lo);
+            *reinterpret_cast<bf16x8*>(p) = hi;
+            if (MODE == kScanX3) *reinterpret_cast<bf16x8*>(p + d1) = lo;
+        }
+        if constexpr (MODE == kScanBoth) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float* dst = pl + n * elems + plain[h];
+                if (isG) *reinterpret_cast<f32x4*>(dst) = x[h];
+                else
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dst[i * dk] = x[h][i];
+            }
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) load(min(1 + u, nc - 1), t[u]);
+    for (int n0 = 0; n0 < nc; n0 += 4 * (kThreads / kWave)) {
+        float gm[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t tok = int64_t(n0 + 4 * wave + u) * 64 + lane;
+            gm[u] = tok < s.seq_len ? a.gamma[bh * s.seq_len + tok] : 1.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float d = wave_prod(gm[u]);
+            if (n0 + 4 * wave + u < nc) sD[n0 + 4 * wave + u] = d;  // every lane holds it
+        }
+    }
+    __syncthreads();
+    f32x4 x[NV];
+#pragma unroll
+    for (int h = 0; h < NV; ++h) x[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    store(0, x);
+    for (int n = 1; n < nc; n += kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (n + u < nc) {
+                const float d = sD[n + u - 1];
+#pragma unroll
+                for (int h = 0; h < NV; ++h) x[h] = t[u][h] + d * x[h];
+                store(n + u, x);
+                load(min(n + u + kAhead, nc - 1), t[u]);
+            }
+    }
+}
+
+template <int MODE>
+hipError_t launch_scan(const StateArgs& a, int64_t part2, hipStream_t stream)
+{
+    const int64_t bh = a.s.batch * a.s.heads;
+    const int per = a.s.d_k * (a.s.d_k + a.s.d_v) / (MODE == kScanPlain ? 4 : 8);
+    hipLaunchKernelGGL(chunk_scan_kernel<MODE>, dim3(unsigned(bh * (per / kThreads))), dim3(kThreads), 0, stream, a, part2);
+    return hipGetLastError();
+}
+
 // Segments of the wide scan for bh sequences of n_chunks chunks: doubled while the
 // (sequence, part, segment) workgroups still fit the compute units once (the kernel's
 // LDS allows one workgroup per unit) and each segment keeps at least kMinSegChunks
@@ -853,7 +1049,34 @@ hipError_t launch_wide(const StateArgs& a, hipStream_t stream)
         S = 1;
         len = nc;
     }
-    SegPlan sg{len, S, 0, S, false, slots, a.seg_ws, S > 1 ? a.seg_ws + tot_elems : nullptr};
+    SegPlan sg{len, S, 0, S, false, slots, a.seg_ws, S > 1 ? a.seg_ws + tot_elems : nullptr, 0, 0};
+    // Few, short sequences: the walk is a chain of chunk steps that leaves most of the chip idle
+    // (its segments too: they keep at least kMinSegChunks chunks and the walk runs twice).  The
+    // chunks' own totals side by side and one scan over them replace the chain by the rounds
+    // of the totals, but move the states twice more and add the scan's own chain.  In ns,
+    // fitted to both (us per forward, walk / scan): 4 sequences of 27 chunks d 128 91.4 / 52.4,
+    // 2 of 16 d 64 x 128 45.6 / 28.6, 24 of 16 d 128 x 64 82.3 / 73.3; not 64 of 16 d 128
+    // 134 / 170, 2 of 232 d 64 68.9 / 150, 36 of 10 d 128 71.6 / 78.7.
+    const int64_t step = 600 + int64_t(DK) * (DK + DV) / 20;
+    const int64_t units = (2 * bh * S + kComputeUnits - 1) / kComputeUnits;
+    const int64_t walk_ns = (S > 1 ? 2 * len * step + 5000 : nc * step) * units;
+    const int64_t scan_ns = 6000 + (2 * bh * (nc - 1) + kComputeUnits - 1) / kComputeUnits * step + 450 * nc +
+                            bh * nc * int64_t(DK) * (DK + DV) * 4 / 2700;
+    if (!final_only && !fin && nc > 1 && nc <= kScanChunks && scan_ns < walk_ns) {
+        const int64_t g_plane = bh * nc * int64_t(DV) * DK * 2;
+        const int mode = a.x3 ? kScanX3 : a.Hs32 ? kScanBoth : kScanFrag;
+        // second halves of the totals: x3 the low plane of G, bf16 fragments the other half of
+        // the workspace
+        const int64_t part2 = a.x3 ? g_plane : mode == kScanFrag ? reinterpret_cast<char*>(a.seg_ws) - static_cast<char*>(a.Hs) : 0;
+        if (mode != kScanFrag || (a.seg_ws && a.seg_bytes >= size_t(bh * nc * int64_t(DK) * (DK + DV) * 2))) {
+            const SegPlan p1{1, nc, 0, nc - 1, true, 0, nullptr, nullptr, mode, part2};
+            launch_wide_kernel<DK, DV, false, true>(a, p1, bh, stream);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            return mode == kScanX3 ? launch_scan<kScanX3>(a, part2, stream)
+                 : mode == kScanBoth ? launch_scan<kScanBoth>(a, part2, stream) : launch_scan<kScanFrag>(a, part2, stream);
+        }
+    }
     if (S > 1 && final_only) {
         sg.totals = true;
         launch_wide_kernel<DK, DV, false, true>(a, sg, bh, stream);
@@ -925,8 +1148,21 @@ hipError_t launch_chunk_state(const StateArgs& a, hipStream_t stream)
     }
     if (!a.s.bf16 && a.s.chunk == 64) {
         const unsigned blocks = unsigned(bh * ((a.s.d_k + a.s.d_v) / 16) * (a.s.d_k / 64));
-        auto kern = a.s.d_k == 64 ? (a.store_chunks ? chunk_state_f32_kernel<64, true> : chunk_state_f32_kernel<64, false>)
-                                  : (a.store_chunks ? chunk_state_f32_kernel<128, true> : chunk_state_f32_kernel<128, false>);
+        const int nc = a.s.n_chunks;
+        // the chunks' totals and a scan instead of the walk, as for bf16 inputs (launch_wide; us
+        // per forward, walk / scan: 2 sequences of 232 chunks d 64 223 / 90, 8 of 13 32.1 / 28.1;
+        // not 32 of 32 76.9 / 81.3, 16 of 64 d 128 268 / 309)
+        const int64_t walk_ns = 900 * int64_t(nc) * ((int64_t(blocks) + 511) / 512);
+        const int64_t scan_ns = 6000 + 300 * int64_t(nc) + bh * nc * int64_t(a.s.d_k) * (a.s.d_k + a.s.d_v) * 4 / 2700 +
+                                int64_t(blocks) * (nc - 1);
+        if (a.store_chunks && !a.final_H && !a.final_G && nc > 1 && nc <= kScanChunks && scan_ns < walk_ns) {
+            auto one = a.s.d_k == 64 ? chunk_state_f32_kernel<64, 2> : chunk_state_f32_kernel<128, 2>;
+            hipLaunchKernelGGL(one, dim3(blocks * unsigned(nc - 1)), dim3(kThreads), 0, stream, a);
+            const hipError_t e = hipGetLastError();
+            return e != hipSuccess ? e : launch_scan<kScanPlain>(a, 0, stream);
+        }
+        auto kern = a.s.d_k == 64 ? (a.store_chunks ? chunk_state_f32_kernel<64, 1> : chunk_state_f32_kernel<64, 0>)
+                                  : (a.store_chunks ? chunk_state_f32_kernel<128, 1> : chunk_state_f32_kernel<128, 0>);
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, stream, a);
         return hipGetLastError();
     }

@@ -774,3 +774,23 @@ def test_decode_few_pairs_matches_many_pairs_kernel(dk, dv, packed):
             e = (few[0][same] - other[0][:n][same]).norm() / other[0][:n][same].norm()
             assert float(e) <= 2e-6
         assert not few[0][3].any()
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("dtype,prec", [("bf16", L.MESA_PREC_BF16X3), ("bf16", L.MESA_PREC_BF16), ("f32", L.MESA_PREC_F32)])
+@pytest.mark.parametrize("bh,T", [(1, 15 * 64 + 1), (2, 23 * 64), (3, 36 * 64 + 63), (1, 66 * 64 + 5)])
+def test_chunk_states_from_totals_and_scan(bh, T, dtype, prec, dk, dv):
+    """Few, short sequences: the chunks' own totals and one scan over them instead of the walk,
+    in the three state layouts (fewer and more chunks than the scan keeps in flight, ragged
+    ends).  Gates near one keep every earlier chunk visible, a zero gate resets memory inside
+    a chunk; the workspace starts as NaN, so a state read before it is written shows.  Outputs
+    against the oracle at the tolerance of each precision."""
+    x = W.forward_inputs(1, bh, T, dk, dv, dtype, 5.0, seed=T + dk + dv)
+    x["gamma"][...] = np.maximum(x["gamma"], 0.995).astype(np.float32)
+    x["gamma"][0, bh - 1, T // 2] = 0.0
+    need = L.forward_workspace_bytes(1, bh, T, dk, dv, 64)
+    ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    got = _gpu_forward(x, dtype, 8, 64, precision=prec, workspace=ws)
+    ref = oracle.forward(x["q"], x["k"], x["v"], x["gamma"], x["beta"], x["lam"], 8)["out"]
+    tol = TOL_BF16 if prec == L.MESA_PREC_BF16 else 2e-6 if dtype == "f32" else TOL_F32
+    assert rel_l2(got, ref) <= tol
