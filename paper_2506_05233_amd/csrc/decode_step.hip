@@ -30,10 +30,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Word 3 of a raw buffer resource on gfx9 (32-bit data format, no swizzle).
 constexpr int kBufferRsrcWord3 = 0x00020000;
 constexpr int kXB = 8;  // diagonals per LDS exchange of the packed layout
+// Cache policy of the buffer accesses (their aux operand): the default, or non-temporal.
+constexpr int kKeep = 0, kStream = 2;
 
-template <typename Tin, int DK, int DV, bool PACKED>
-__global__ __launch_bounds__(DK) __attribute__((amdgpu_waves_per_eu(3)))
-void decode_step_kernel(DecodeArgs a)
+template <typename Tin, int DK, int DV, bool PACKED, int AUX>
+__device__ __forceinline__ void decode_step(const DecodeArgs& a)
 {
     constexpr int NW = DK / kWave;  // waves per pair
     const int64_t pair = blockIdx.x;
@@ -76,8 +77,8 @@ void decode_step_kernel(DecodeArgs a)
     float hdiag;
     if constexpr (!PACKED) {
 #pragma unroll
-        for (int c = 0; c < DK; ++c) hc[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * 4, c * DK * 4, 0));
-        hdiag = gam * __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * (DK + 1) * 4, 0, 0)) + bet * kR * kR + lR;
+        for (int c = 0; c < DK; ++c) hc[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * 4, c * DK * 4, AUX));
+        hdiag = gam * __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * (DK + 1) * 4, 0, AUX)) + bet * kR * kR + lR;
         __syncthreads();
 #pragma unroll
         for (int c4 = 0; c4 < DK; c4 += 4) {
@@ -85,24 +86,24 @@ void decode_step_kernel(DecodeArgs a)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 hc[c4 + e] = gam * hc[c4 + e] + bet * kR * kc[e];
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(hc[c4 + e]), hr, tid * 4, (c4 + e) * DK * 4, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(hc[c4 + e]), hr, tid * 4, (c4 + e) * DK * 4, AUX);
             }
         }
     } else {
         constexpr int HALF = DK / 2;
         const int rl = tid % HALF;  // the owner of this thread's last-diagonal entry
 #pragma unroll
-        for (int k = 0; k < HALF; ++k) ho[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * 4, k * DK * 4, 0));
-        ho[HALF] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, rl * 4, HALF * DK * 4, 0));
+        for (int k = 0; k < HALF; ++k) ho[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * 4, k * DK * 4, AUX));
+        ho[HALF] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, rl * 4, HALF * DK * 4, AUX));
         __syncthreads();
         const float bkR = bet * kR;
 #pragma unroll
         for (int k = 0; k < HALF; ++k) {
             ho[k] = gam * ho[k] + bkR * sk[tid + k];
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ho[k]), hr, tid * 4, k * DK * 4, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ho[k]), hr, tid * 4, k * DK * 4, AUX);
         }
         ho[HALF] = gam * ho[HALF] + (bet * sk[rl]) * sk[rl + HALF];
-        if (tid < HALF) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ho[HALF]), hr, tid * 4, HALF * DK * 4, 0);
+        if (tid < HALF) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ho[HALF]), hr, tid * 4, HALF * DK * 4, AUX);
         // H[R][R - k] is thread (R - k)'s updated entry of diagonal k: exchanged through
         // LDS, kXB diagonals at a time
 #pragma unroll
@@ -200,7 +201,7 @@ void decode_step_kernel(DecodeArgs a)
     const __amdgpu_buffer_rsrc_t gr = __builtin_amdgcn_make_buffer_rsrc(Gp, 0, DV * DK * 4, kBufferRsrcWord3);
     float gc[DV];
 #pragma unroll
-    for (int e = 0; e < DV; ++e) gc[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, tid * 4, e * DK * 4, 0));
+    for (int e = 0; e < DV; ++e) gc[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, tid * 4, e * DK * 4, AUX));
     const float bk = bet * kR;
 #pragma unroll
     for (int e4 = 0; e4 < DV; e4 += 4) {
@@ -208,7 +209,7 @@ void decode_step_kernel(DecodeArgs a)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             gc[e4 + q] = gam * gc[e4 + q] + bk * ve[q];
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(gc[e4 + q]), gr, tid * 4, (e4 + q) * DK * 4, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(gc[e4 + q]), gr, tid * 4, (e4 + q) * DK * 4, AUX);
             gc[e4 + q] *= x;
         }
     }
@@ -247,6 +248,18 @@ void decode_step_kernel(DecodeArgs a)
         for (int u = 1; u < NW; ++u) o += so[u][e];
         a.out[pair * DV + e] = o;
     }
+}
+
+template <typename Tin, int DK, int DV, bool PACKED>
+__global__ __launch_bounds__(DK) __attribute__((amdgpu_waves_per_eu(3))) void decode_step_kernel(DecodeArgs a)
+{
+    decode_step<Tin, DK, DV, PACKED, kKeep>(a);
+}
+// the same with non-temporal state traffic
+template <typename Tin, int DK, int DV, bool PACKED>
+__global__ __launch_bounds__(DK) __attribute__((amdgpu_waves_per_eu(3))) void decode_stream_kernel(DecodeArgs a)
+{
+    decode_step<Tin, DK, DV, PACKED, kStream>(a);
 }
 
 // Few pairs (see launch_dk): the step is then one chain of dependent products, and the kernel
@@ -485,10 +498,15 @@ hipError_t launch_dk(const DecodeArgs& a, hipStream_t stream)
             hipLaunchKernelGGL((decode_few_kernel<Tin, DK, 128, PACKED>), dim3(blocks), dim3(DK * 4), 0, stream, a);
         return hipGetLastError();
     }
-    if (a.d_v == 64)
-        hipLaunchKernelGGL((decode_step_kernel<Tin, DK, 64, PACKED>), dim3(blocks), dim3(DK), 0, stream, a);
-    else
-        hipLaunchKernelGGL((decode_step_kernel<Tin, DK, 128, PACKED>), dim3(blocks), dim3(DK), 0, stream, a);
+    // States that outgrow the 256 MB last-level cache are streamed past the caches, which the
+    // next step would find holding other pairs anyway (us per step, streamed against kept: 4096
+    // pairs d 128 213.5 / 217.5, packed 171 / 184, d 128 x 64 164 / 167; within the cache it
+    // costs: 1024 pairs d 128 58.0 / 53.9, 4096 of d 64 57.7 / 55.1).
+    const int64_t bytes = int64_t(blocks) * DK * ((PACKED ? DK / 2 + 1 : DK) + a.d_v) * 4;
+    const bool big = bytes > (int64_t(256) << 20);
+    auto kern = a.d_v == 64 ? (big ? decode_stream_kernel<Tin, DK, 64, PACKED> : decode_step_kernel<Tin, DK, 64, PACKED>)
+                            : (big ? decode_stream_kernel<Tin, DK, 128, PACKED> : decode_step_kernel<Tin, DK, 128, PACKED>);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(DK), 0, stream, a);
     return hipGetLastError();
 }
 
