@@ -33,6 +33,9 @@ constexpr int kXB = 8;  // diagonals per LDS exchange of the packed layout
 // Cache policy of the buffer accesses (their aux operand): the default, or non-temporal.
 constexpr int kKeep = 0, kStream = 2;
 
+// gamma s + b c with one rounding order, so that every kernel leaves the same states
+__device__ __forceinline__ float updated(float gamma, float s, float b, float c) { return fmaf(gamma, s, b * c); }
+
 template <typename Tin, int DK, int DV, bool PACKED, int AUX>
 __device__ __forceinline__ void decode_step(const DecodeArgs& a)
 {
@@ -78,14 +81,14 @@ __device__ __forceinline__ void decode_step(const DecodeArgs& a)
     if constexpr (!PACKED) {
 #pragma unroll
         for (int c = 0; c < DK; ++c) hc[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * 4, c * DK * 4, AUX));
-        hdiag = gam * __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * (DK + 1) * 4, 0, AUX)) + bet * kR * kR + lR;
+        hdiag = updated(gam, __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(hr, tid * (DK + 1) * 4, 0, AUX)), bet * kR, kR) + lR;
         __syncthreads();
 #pragma unroll
         for (int c4 = 0; c4 < DK; c4 += 4) {
             const f32x4 kc = *reinterpret_cast<const f32x4*>(sk + c4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                hc[c4 + e] = gam * hc[c4 + e] + bet * kR * kc[e];
+                hc[c4 + e] = updated(gam, hc[c4 + e], bet * kR, kc[e]);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(hc[c4 + e]), hr, tid * 4, (c4 + e) * DK * 4, AUX);
             }
         }
@@ -99,10 +102,10 @@ __device__ __forceinline__ void decode_step(const DecodeArgs& a)
         const float bkR = bet * kR;
 #pragma unroll
         for (int k = 0; k < HALF; ++k) {
-            ho[k] = gam * ho[k] + bkR * sk[tid + k];
+            ho[k] = updated(gam, ho[k], bkR, sk[tid + k]);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ho[k]), hr, tid * 4, k * DK * 4, AUX);
         }
-        ho[HALF] = gam * ho[HALF] + (bet * sk[rl]) * sk[rl + HALF];
+        ho[HALF] = updated(gam, ho[HALF], bet * sk[rl], sk[rl + HALF]);
         if (tid < HALF) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ho[HALF]), hr, tid * 4, HALF * DK * 4, AUX);
         // H[R][R - k] is thread (R - k)'s updated entry of diagonal k: exchanged through
         // LDS, kXB diagonals at a time
@@ -208,7 +211,7 @@ __device__ __forceinline__ void decode_step(const DecodeArgs& a)
         const f32x4 ve = *reinterpret_cast<const f32x4*>(sv + e4);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            gc[e4 + q] = gam * gc[e4 + q] + bk * ve[q];
+            gc[e4 + q] = updated(gam, gc[e4 + q], bk, ve[q]);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(gc[e4 + q]), gr, tid * 4, (e4 + q) * DK * 4, AUX);
             gc[e4 + q] *= x;
         }
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(DK * 4) void decode_few_kernel(DecodeArgs a)
         for (int e = 0; e < EC; ++e) {
             const f32x4 kc = *reinterpret_cast<const f32x4*>(sk + 16 * e + 4 * g);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) hr[e][i] = gam * hr[e][i] + bet * kc[i] * kr;
+            for (int i = 0; i < 4; ++i) hr[e][i] = updated(gam, hr[e][i], bet * kc[i], kr);
         }
     } else {
 #pragma unroll
@@ -351,7 +354,7 @@ __global__ __launch_bounds__(DK * 4) void decode_few_kernel(DecodeArgs a)
             if (o >= NH * DK) continue;
             const int k = o / DK, i0 = o % DK;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) hp[u][i] = gam * hp[u][i] + bet * sk[i0 + i] * sk[(i0 + i + k) % DK];
+            for (int i = 0; i < 4; ++i) hp[u][i] = updated(gam, hp[u][i], bet * sk[i0 + i], sk[(i0 + i + k) % DK]);
             *reinterpret_cast<f32x4*>(sh + o) = hp[u];
         }
         __syncthreads();
@@ -470,7 +473,7 @@ __global__ __launch_bounds__(DK * 4) void decode_few_kernel(DecodeArgs a)
         for (int e = 0; e < EC; ++e) {
             const f32x4 kc = *reinterpret_cast<const f32x4*>(sk + 16 * e + 4 * g);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) gr[t][e][i] = gam * gr[t][e][i] + bet * kc[i] * ve;
+            for (int i = 0; i < 4; ++i) gr[t][e][i] = updated(gam, gr[t][e][i], bet * kc[i], ve);
             *reinterpret_cast<f32x4*>(Gp + (r0 + n) * DK + 16 * e + 4 * g) = gr[t][e];
         }
         const float o = row_dot(gr[t]);
