@@ -411,19 +411,49 @@ __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
     }
 }
 
+// A token-major tile of 64 rows of D bf16 in LDS: 16-byte piece c of token i sits at piece
+// c ^ (i mod D / 8) of its row, which spreads the rows' writes and the transposing reads below
+// evenly over the banks.
+template <int D>
+__device__ __forceinline__ uint16_t* tile_piece(uint16_t* tile, int tok, int c)
+{
+    return tile + tok * D + 8 * (c ^ (tok % (D / 8)));
+}
+
+// Operand fragment with rows (or columns) = features 16 t + n, contraction = tokens 32 u ..:
+// two transposing reads (of each 16 lanes, lane l points at four features of row l / 4; lane n
+// receives feature n of the four rows).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+template <int D>
+__device__ __forceinline__ bf16x8 tile_col_frag(uint16_t* tile, int t, int u, int g, int n)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint2 r[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int tl = 4 * g + n / 4;  // token within its 16
+        uint16_t* src = tile + (32 * u + 16 * h) * D + tl * D + 8 * ((2 * t + n % 4 / 2) ^ (tl % (D / 8))) + 4 * (n % 2);
+        r[h] = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src)));
+    }
+    return __builtin_bit_cast(bf16x8, make_uint4(r[0].x, r[0].y, r[1].x, r[1].y));
+#else
+    return bf16x8{};
+#endif
+}
+
 // Wide variant (bf16 k and v, chunk 64, d_k and d_v in {64, 128}), used for the
 // bf16 fragment chunk states and for the states-only call.  Two workgroups share the
 // state of one (batch, head) sequence -- part 0 is H (d_k x d_k), part 1 is G^T
 // (d_k x d_v), both as [key feature R][column c] -- in registers, and walk its chunks
 // in order:
 //
-//   X_{next} = D X + K^T (w ⊙ Y),   Y = K (part 0) or V (part 1), w_i = beta_i zeta_{end,i}.
+//   X_{next} = D X + (w ⊙ K)^T Y,   Y = K (part 0) or V (part 1), w_i = beta_i zeta_{end,i}.
 //
 // With d_k = d_v and single products each workgroup owns half of the columns of both
 // parts, so both read the same bytes (k and half of v) and write the same share of the
 // states; otherwise one workgroup owns H and the other G^T.
 //
-// When fp32 states leave the kernel (the final states), w ⊙ Y is split into bf16
+// When fp32 states leave the kernel (the final states), w ⊙ K is split into bf16
 // high and low parts (two products, ~16-bit weights, states fp32-accurate); when
 // only the bf16 chunk states are produced, the high part alone is used: its
 // rounding (2^-9 per term, averaged over the chunk's 64 terms) stays well below the
@@ -433,7 +463,10 @@ __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
 // (CS = 8 / NS); its 16x16 result tiles pair up into complete bf16 A-fragments of
 // the fragment layout (rows 32s.. of X^T are fragment row block s), so every chunk
 // state is written with whole 1-KiB wave stores.  Staging is double-buffered in LDS
-// (one barrier per chunk); the inputs of chunk n + 3 are loaded into registers while
+// (one barrier per chunk) and token-major: a thread scales 8 features of a token and writes them
+// in 16-byte pieces, and the transposing LDS reads turn the tiles into operands (transposed by
+// the staging stores instead, four bytes at a time: B8 H16 T2048 d 128 split 147 us, now 129;
+// states only, 64 sequences of 4001 tokens, 72 us, now 62); the inputs of chunk n + 3 are loaded into registers while
 // chunk n is consumed (a chunk's work is shorter than a memory round trip under
 // load), and the staging of chunk n + 1 is interleaved with the products of chunk n.
 //
@@ -446,7 +479,7 @@ __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
 // applied to whole segments -- and walks the segment's chunks as above.  A states-only call
 // needs no second walk: all its segments run side by side in the first launch and a small
 // kernel combines their totals (4 x 16 sequences of 4001 tokens, d 128: 140 us with the last
-// segment walked after the others, 78 us combined).
+// segment walked after the others, 62 us combined).
 constexpr int kWideThreads = 512;  // eight waves: two per SIMD
 
 // Segments of one launch of the wide scan.
@@ -475,10 +508,8 @@ template <int DK, int DV, bool STORE, bool SPLIT, bool PLAIN = false, bool X3 = 
 __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArgs a, SegPlan sg)
 {
     constexpr int C = 64;
-    constexpr int LDT = C + 4;           // row stride of the [feature][token] tiles (34 words: see above)
     constexpr int NS = DK / 32;          // 32-row blocks of the key features
     constexpr int CS = kWideThreads / kWave / NS;  // column shares per row block
-    constexpr int FPP = 8 * kWideThreads / 32;     // features staged per pass (8 per thread group)
     const ForwardShape s = a.s;
     const int blk = xcd_major_block(blockIdx.x, gridDim.x);  // the two halves of a segment share an L2
     // d_k = d_v, bf16 states only: workgroup `half` owns H's columns and G^T's columns
@@ -493,16 +524,18 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = tid % kWave;
     const int g = lane / 16, ln = lane % 16;
-    const int p = tid % 32, fg = tid / 32;  // staging: tokens 2p, 2p+1, features 8 fg + FPP m ..
 
-    __shared__ __attribute__((aligned(16))) uint16_t sA[2][DK * LDT];                           // k_i[R], [R][i]
-    __shared__ __attribute__((aligned(16))) uint16_t sBh[2][(DK > DV ? DK : DV) * LDT];         // hi(w_i y_i[c]), [c][i]
-    __shared__ __attribute__((aligned(16))) uint16_t sBl[2][(DK > DV ? DK : DV) * LDT];         // lo(w_i y_i[c])
+    constexpr int DM = DK > DV ? DK : DV;
+    __shared__ __attribute__((aligned(16))) uint16_t sAh[2][C * DK];               // hi(w_i k_i)
+    __shared__ __attribute__((aligned(16))) uint16_t sAl[2][SPLIT ? C * DK : 8];   // lo(w_i k_i)
+    __shared__ __attribute__((aligned(16))) uint16_t sB[2][C * DM];                // y_i
 
     auto run = [&](auto nc_tag) {
         constexpr int NC = decltype(nc_tag)::value;  // columns of this workgroup
         constexpr int NCT = NC / 16 / CS;            // 16-column tiles of this wave
-        constexpr int NKQ = (DK + FPP - 1) / FPP, NY = (NC + FPP - 1) / FPP;  // staging passes
+        // staging: 16-byte pieces of k and of y per thread (8 features of a token each)
+        constexpr int PK = DK / 8, PY = NC / 8, NK = C * PK / kWideThreads, NY = C * PY / kWideThreads;
+        static_assert(NK * kWideThreads == C * PK && NY * kWideThreads == C * PY, "whole passes");
         const int sblk = wave % NS, cs = wave / NS;
         // Staged y column c: balanced, k feature c if c lies in this half's own region
         // (c / (NC/2) == half), else v feature half * NC/2 + c % (NC/2); otherwise k (half 0)
@@ -516,8 +549,8 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
         const uint16_t* vp = static_cast<const uint16_t*>(a.v);
 
         struct Regs {
-            uint4 k[NKQ][2];  // k of tokens 2p, 2p+1, features 64m + 8fg ..
-            uint4 y[NY][2];   // y of the same tokens (v; unused for H, whose y is k)
+            uint4 k[NK];
+            uint4 y[NY];  // v pieces (unused where y is k)
             float gam, bet;
             int valid;
         };
@@ -529,30 +562,25 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             const int lt = min(lane, valid - 1);
             R.gam = a.gamma[tok0 + lt];
             R.bet = a.beta[tok0 + lt];
-            const int64_t r0 = tok0 + min(2 * p, valid - 1), r1 = tok0 + min(2 * p + 1, valid - 1);
-            // feature offsets beyond the row wrap into it (those threads stage nothing)
 #pragma unroll
-            for (int m = 0; m < NKQ; ++m) {
-                const int f0 = (FPP * m + 8 * fg) % DK;
-                R.k[m][0] = *reinterpret_cast<const uint4*>(kp + r0 * DK + f0);
-                R.k[m][1] = *reinterpret_cast<const uint4*>(kp + r1 * DK + f0);
+            for (int m = 0; m < NK; ++m) {
+                const int i = tid + m * kWideThreads;
+                R.k[m] = *reinterpret_cast<const uint4*>(kp + (tok0 + min(i / PK, valid - 1)) * DK + 8 * (i % PK));
             }
 #pragma unroll
             for (int m = 0; m < NY; ++m) {
-                const int f0 = (FPP * m + 8 * fg) % NC;
-                if (y_from_k(f0)) continue;  // wave-uniform: k is already in R.k
+                const int i = tid + m * kWideThreads, f0 = 8 * (i % PY);
+                if (y_from_k(f0)) continue;  // k is already in R.k
                 const int vf = BAL ? half * (NC / 2) + f0 % (NC / 2) : f0;
-                R.y[m][0] = *reinterpret_cast<const uint4*>(vp + r0 * DV + vf);
-                R.y[m][1] = *reinterpret_cast<const uint4*>(vp + r1 * DV + vf);
+                R.y[m] = *reinterpret_cast<const uint4*>(vp + (tok0 + min(i / PY, valid - 1)) * DV + vf);
             }
         };
-        // Staging of a chunk into buffer b, in three pieces that the chunk loop interleaves
-        // with the previous chunk's products: the gate scan (write weights w_i = beta_i
-        // zeta_{end,i} of this thread's two tokens, and the chunk decay D), the key tile, and
-        // the weighted y tile split into bf16 high and low parts (features q0 .. q1-1 of this
-        // thread's group).
+        // Staging of a chunk into buffer b, in pieces that the chunk loop interleaves with the
+        // previous chunk's products: the gate scan (weights w_i = beta_i zeta_{end,i} of this
+        // thread's tokens, zero past the end, and the chunk decay D), the weighted keys split into
+        // bf16 high and low parts, and y as it is.
         struct Gate {
-            float w0, w1, D;
+            float w[NK], D;
         };
         auto gates = [&](const Regs& R) -> Gate {
             const bool live = lane < R.valid;
@@ -562,39 +590,32 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             const float lgE = lane_value(lg, C - 1);
             const int zlE = lane_value(zl, C - 1);
             const float wl = live ? R.bet * (zlE > lane ? 0.0f : expf(lgE - lg)) : 0.0f;
-            return Gate{shfl_lane(wl, 2 * p), shfl_lane(wl, 2 * p + 1), zlE >= 0 ? 0.0f : expf(lgE)};
-        };
-        auto stage_k = [&](const Regs& R, int b) {
-            const bool k0 = 2 * p < R.valid, k1 = 2 * p + 1 < R.valid;
+            Gate gt;
 #pragma unroll
-            for (int m = 0; m < NKQ; ++m) {
-                if (FPP * m + 8 * fg >= DK) continue;
-                const uint4 ka = k0 ? R.k[m][0] : make_uint4(0, 0, 0, 0);
-                const uint4 kb = k1 ? R.k[m][1] : make_uint4(0, 0, 0, 0);
-                stage_token_pair(reinterpret_cast<uint32_t*>(sA[b]), LDT / 2, FPP * m + 8 * fg, p, ka, kb);
-            }
+            for (int m = 0; m < NK; ++m) gt.w[m] = shfl_lane(wl, (tid + m * kWideThreads) / PK);
+            gt.D = zlE >= 0 ? 0.0f : expf(lgE);
+            return gt;
         };
-        auto stage_y = [&](const Regs& R, int b, const Gate& gt, int q0, int q1) {
+        auto stage_k = [&](const Regs& R, int b, const Gate& gt, int m) {
+            const int i = tid + m * kWideThreads;
+            const uint32_t x[4] = {R.k[m].x, R.k[m].y, R.k[m].z, R.k[m].w};
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float va = gt.w[m] * __uint_as_float(x[q] << 16), vb = gt.w[m] * __uint_as_float(x[q] & 0xffff0000u);
+                hi[q] = pack_bf16x2(va, vb);
+                if (SPLIT) lo[q] = pack_bf16x2(va - __uint_as_float(hi[q] << 16), vb - __uint_as_float(hi[q] & 0xffff0000u));
+            }
+            *reinterpret_cast<uint4*>(tile_piece<DK>(sAh[b], i / PK, i % PK)) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            if (SPLIT) *reinterpret_cast<uint4*>(tile_piece<DK>(sAl[b], i / PK, i % PK)) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        };
+        auto stage_y = [&](const Regs& R, int b) {
 #pragma unroll
             for (int m = 0; m < NY; ++m) {
-                if (FPP * m + 8 * fg >= NC) continue;
-                const bool fk = m < NKQ && y_from_k(FPP * m + 8 * fg);
-                const uint4 ya = fk ? R.k[m < NKQ ? m : 0][0] : R.y[m][0];
-                const uint4 yb = fk ? R.k[m < NKQ ? m : 0][1] : R.y[m][1];
-                const uint32_t a4[4] = {ya.x, ya.y, ya.z, ya.w};
-                const uint32_t b4[4] = {yb.x, yb.y, yb.z, yb.w};
-                uint32_t* hi32 = reinterpret_cast<uint32_t*>(sBh[b]);
-                uint32_t* lo32 = reinterpret_cast<uint32_t*>(sBl[b]);
-#pragma unroll
-                for (int q = q0; q < q1; ++q) {
-                    // feature q of tokens 2p and 2p+1: bf16 bits widened by a shift or a mask
-                    const float va = gt.w0 * __uint_as_float((q & 1) ? (a4[q / 2] & 0xffff0000u) : (a4[q / 2] << 16));
-                    const float vb = gt.w1 * __uint_as_float((q & 1) ? (b4[q / 2] & 0xffff0000u) : (b4[q / 2] << 16));
-                    const uint32_t h2 = pack_bf16x2(va, vb);
-                    const int c = FPP * m + 8 * fg + q;
-                    hi32[c * (LDT / 2) + p] = h2;
-                    if (SPLIT) lo32[c * (LDT / 2) + p] = pack_bf16x2(va - __uint_as_float(h2 << 16), vb - __uint_as_float(h2 & 0xffff0000u));
-                }
+                const int i = tid + m * kWideThreads;
+                // where y is k, its pieces are the k pieces (the tiles are then equally wide)
+                const uint4 y = (m < NK && y_from_k(8 * (i % PY))) ? R.k[m < NK ? m : 0] : R.y[m];
+                *reinterpret_cast<uint4*>(tile_piece<NC>(sB[b], i / PY, i % PY)) = y;
             }
         };
 
@@ -614,10 +635,16 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             return part ? c * DK + R : R * DK + c;
         };
 
-        // chunk n: its state is stored, then acc = D acc + K^T (w ⊙ Y) from buffer n % 2;
+        // chunk n: its state is stored, then acc = D acc + (w ⊙ K)^T Y from buffer n % 2;
         // chunk n + 1 is staged (from Rn1) into the other buffer and chunk n + 3 loaded
         float dprod = 1.0f;  // decay across the chunks walked so far
         auto consume = [&](int n, float D, Regs& Rn1, Regs& Rfree, float& Dnext) {
+            // Rfree held this chunk's inputs, staged by now.  The loads are unconditional, so memory
+            // waits count statically; ahead of the state's stores on the single-product walk, after
+            // them on the split one, whose 64 KB of stores per chunk they would hold up (us at B8
+            // H16 T2048 d 128, before / after the stores: 86 / 88 single, 140 / 129 split; at the
+            // end of the step 88 and 133).
+            if (!SPLIT) load(min(n + 3, nend - 1), Rfree);
             if (frag_out && X3 && part == 0) {
                 // H_c as fp32 fragments: half e of fragment f, lane l at [(2 f + e) 64 + l] x 4
                 float* base = static_cast<float*>(a.Hs) + (bh * s.n_chunks + n) * int64_t(kStateElems);
@@ -657,6 +684,7 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
 #pragma unroll
                         for (int ii = 0; ii < 4; ++ii) dst[tile_off(rt, ct, ii)] = acc[rt][ct][ii];
             }
+            if (SPLIT && !PLAIN) load(min(n + 3, nend - 1), Rfree);
             const int b = (n - nbeg) % 2;
             dprod *= D;
 #pragma unroll
@@ -666,25 +694,24 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             // every operand of this chunk's products is read from LDS first; the products then
             // run in three batches with the staging pieces of the next chunk (into the other
             // buffer) between them, and scheduling barriers keep that order
-            bf16x8 af[C / 32][2], bfh[C / 32][NCT], bfl[C / 32][NCT];
+            bf16x8 ah[C / 32][2], al[C / 32][2], bf[C / 32][NCT];
 #pragma unroll
             for (int u = 0; u < C / 32; ++u) {
 #pragma unroll
-                for (int rt = 0; rt < 2; ++rt) af[u][rt] = lds_frag(sA[b] + (32 * sblk + 16 * rt + ln) * LDT + 32 * u + 4 * g);
-#pragma unroll
-                for (int ct = 0; ct < NCT; ++ct) {
-                    const int c = 16 * (lct0 + ct) + ln;
-                    bfh[u][ct] = lds_frag(sBh[b] + c * LDT + 32 * u + 4 * g);
-                    if (SPLIT) bfl[u][ct] = lds_frag(sBl[b] + c * LDT + 32 * u + 4 * g);
+                for (int rt = 0; rt < 2; ++rt) {
+                    ah[u][rt] = tile_col_frag<DK>(sAh[b], 2 * sblk + rt, u, g, ln);
+                    if (SPLIT) al[u][rt] = tile_col_frag<DK>(sAl[b], 2 * sblk + rt, u, g, ln);
                 }
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) bf[u][ct] = tile_col_frag<NC>(sB[b], lct0 + ct, u, g, ln);
             }
             auto products = [&](int u, int ct_lo, int ct_hi) {
 #pragma unroll
                 for (int ct = ct_lo; ct < ct_hi; ++ct)
 #pragma unroll
                     for (int rt = 0; rt < 2; ++rt) {
-                        acc[rt][ct] = mfma16(af[u][rt], bfh[u][ct], acc[rt][ct]);
-                        if (SPLIT) acc[rt][ct] = mfma16(af[u][rt], bfl[u][ct], acc[rt][ct]);
+                        acc[rt][ct] = mfma16(ah[u][rt], bf[u][ct], acc[rt][ct]);
+                        if (SPLIT) acc[rt][ct] = mfma16(al[u][rt], bf[u][ct], acc[rt][ct]);
                     }
             };
             const int bn = (n - nbeg + 1) % 2;  // a chunk past the end stages into a buffer nobody reads
@@ -692,13 +719,13 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             const Gate gt = gates(Rn1);
             __builtin_amdgcn_sched_barrier(0);
             products(1, 0, NCT / 2);
-            stage_k(Rn1, bn);
-            stage_y(Rn1, bn, gt, 0, 4);
+            stage_y(Rn1, bn);
+            stage_k(Rn1, bn, gt, 0);
             __builtin_amdgcn_sched_barrier(0);
             products(1, NCT / 2, NCT);
-            stage_y(Rn1, bn, gt, 4, 8);
+            if (NK > 1) stage_k(Rn1, bn, gt, NK - 1);
             Dnext = gt.D;
-            load(min(n + 3, nend - 1), Rfree);  // unconditional, so memory waits count statically
+            if (PLAIN) load(min(n + 3, nend - 1), Rfree);  // earlier, its addresses spill
             __syncthreads();
         };
 
@@ -743,8 +770,9 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
         float D0, D1 = 1.0f, D2 = 1.0f;
         {
             const Gate gt = gates(R0);
-            stage_k(R0, 0);
-            stage_y(R0, 0, gt, 0, 8);
+#pragma unroll
+            for (int m = 0; m < NK; ++m) stage_k(R0, 0, gt, m);
+            stage_y(R0, 0);
             D0 = gt.D;
         }
         __syncthreads();
