@@ -104,14 +104,20 @@ __device__ __forceinline__ float shfl_lane(float x, int src)
 //     prod_{s=i+1..j} gamma_s = (zl[j] > i) ? 0 : exp(lg[j] - lg[i])
 //     prod_{s=0..j}   gamma_s = (zl[j] >= 0) ? 0 : exp(lg[j]).
 // A zero gate therefore resets memory exactly instead of producing log(0).
-__device__ __forceinline__ void chunk_log_decays(const float* gamma, int valid, float* lg, int* zl)
+// log_decays_of takes the lane's gate (loaded by the caller, ahead of other loads).
+__device__ __forceinline__ void log_decays_of(float g, int valid, float* lg, int* zl)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const float g = lane < valid ? gamma[lane] : 1.0f;
     const float s = wave_scan_add(g > 0.0f ? logf(g) : 0.0f);
     const int z = wave_scan_max((lane < valid && !(g > 0.0f)) ? lane : -1);
     lg[lane] = s;
     zl[lane] = z;
+}
+
+__device__ __forceinline__ void chunk_log_decays(const float* gamma, int valid, float* lg, int* zl)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    log_decays_of(lane < valid ? gamma[lane] : 1.0f, valid, lg, zl);
 }
 
 // prod_{s=i+1..j} gamma_s for in-chunk tokens i <= j (1 when i == j), 0 for i > j.
