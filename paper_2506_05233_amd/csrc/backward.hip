@@ -1426,37 +1426,38 @@ __global__ __launch_bounds__(kThreads) void bwd_adjoint_scan_kernel(BwdArgs a, c
 
 // ---------------------------------------------------------------- dLambda
 // dLambda[h][b] = sum over the batch and the chunks of the per-chunk partial sums:
-// one workgroup per head; thread (b, slot) sums every kThreads / d_k-th (batch, chunk)
-// entry, eight loads in flight at a time into eight partial sums, then the partial
-// sums and the slots are combined in a fixed order.
-__global__ __launch_bounds__(kThreads) void bwd_dlam_kernel(BwdArgs a)
+// one workgroup per head and sixteen features (64 bytes of a row); thread (slot, b) sums
+// every kLamSlots-th (batch, chunk) entry, eight loads in flight at a time into eight
+// partial sums, then the partial sums and the slots are combined in a fixed order.  Bound by
+// the round trips of its loads: B8 H16 T2048 d128 5.7 us, one workgroup per head of four waves
+// 26.3 and of sixteen 13.6.
+constexpr int kLamCols = 16, kLamSlots = 64;
+__global__ __launch_bounds__(kLamCols * kLamSlots) void bwd_dlam_kernel(BwdArgs a)
 {
     const ForwardShape s = a.s;
-    const int dk = s.d_k, slots = kThreads / dk;
-    const int64_t h = blockIdx.x;
-    const int b = threadIdx.x % dk, slot = threadIdx.x / dk;
+    const int dk = s.d_k, parts = dk / kLamCols;
+    const int64_t h = blockIdx.x / parts;
+    const int col = threadIdx.x % kLamCols, slot = threadIdx.x / kLamCols;
+    const int b = int(blockIdx.x % parts) * kLamCols + col;
     const int64_t per = s.batch * s.n_chunks;  // partial sums of this head
-    __shared__ float sAcc[kThreads];
-    auto part = [&](int64_t e) {
-        const int64_t bb = e / s.n_chunks, n = e % s.n_chunks;
-        return a.dlam_part[((bb * s.heads + h) * s.n_chunks + n) * dk + b];
-    };
+    __shared__ float sAcc[kLamCols * kLamSlots];
     float acc8[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    int64_t e = slot;
-    for (; e + 7 * slots < per; e += 8 * slots) {
+    for (int64_t e0 = slot; e0 < per; e0 += 8 * kLamSlots) {
         float v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = part(e + u * slots);
+        for (int u = 0; u < 8; ++u) {
+            const int64_t e = min<int64_t>(e0 + u * kLamSlots, per - 1);
+            const int64_t bb = e / s.n_chunks, n = e % s.n_chunks;
+            v[u] = a.dlam_part[((bb * s.heads + h) * s.n_chunks + n) * dk + b];
+        }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc8[u] += v[u];
+        for (int u = 0; u < 8; ++u) acc8[u] += e0 + u * kLamSlots < per ? v[u] : 0.0f;
     }
-    for (; e < per; e += slots) acc8[0] += part(e);
-    const float acc = ((acc8[0] + acc8[1]) + (acc8[2] + acc8[3])) + ((acc8[4] + acc8[5]) + (acc8[6] + acc8[7]));
-    sAcc[threadIdx.x] = acc;
+    sAcc[threadIdx.x] = ((acc8[0] + acc8[1]) + (acc8[2] + acc8[3])) + ((acc8[4] + acc8[5]) + (acc8[6] + acc8[7]));
     __syncthreads();
     if (slot == 0) {
         float t = 0.0f;
-        for (int u = 0; u < slots; ++u) t += sAcc[u * dk + b];
+        for (int u = 0; u < kLamSlots; ++u) t += sAcc[u * kLamCols + col];
         a.dlam[h * dk + b] = t;
     }
 }
@@ -1520,7 +1521,7 @@ hipError_t launch_bwd_dims(const BwdArgs& a, hipStream_t stream, int stage)
             hipLaunchKernelGGL((bwd_grad_kernel<Tin, DK, DV>), dim3(chunks), dim3(kGradThreads), 0, stream, a);
             break;
         default:
-            hipLaunchKernelGGL(bwd_dlam_kernel, dim3(unsigned(a.s.heads)), dim3(kThreads), 0, stream, a);
+            hipLaunchKernelGGL(bwd_dlam_kernel, dim3(unsigned(a.s.heads * (a.s.d_k / kLamCols))), dim3(kLamCols * kLamSlots), 0, stream, a);
     }
     return hipGetLastError();
 }

@@ -212,3 +212,23 @@ def test_adjoints_from_totals_and_scan(bh, T, dk, dv, dtype):
     tol = 2e-2 if dtype == "bf16" else 1e-5
     for name in ("dq", "dk", "dv", "dgamma", "dbeta", "dlam"):
         assert rel_l2(g[name].cpu().numpy(), ref[name]) <= tol, name
+
+
+@pytest.mark.parametrize("B,dk", [(15, 64), (16, 128), (33, 64), (129, 128), (300, 64)])
+def test_lambda_gradient_sums_every_chunk(B, dk):
+    """dLambda over batches whose (batch, chunk) entries leave slots of the reduction empty (60),
+    fill each once (64), leave a second pass ragged (132), and go past its eight loads a pass
+    (516, 1200): the sum, in 64 bits, of the dLambda of groups of four sequences."""
+    H, T = 2, 3 * 64 + 5
+    x = W.forward_inputs(B, H, T, dk, 64, "f32", 4.0, seed=B)
+    d = to_device(x, "f32")
+    dout = torch.from_numpy(_dout(x, B)).cuda()
+
+    def dlam(lo, hi):
+        s = {n: d[n][lo:hi].contiguous() for n in ("q", "k", "v", "gamma", "beta")}
+        f = L.forward(s["q"], s["k"], s["v"], s["gamma"], s["beta"], d["lam"], 10, 64, want_qstar=True)
+        g = L.backward(s["k"], s["v"], s["gamma"], s["beta"], d["lam"], f["qstar"], dout[lo:hi].contiguous(), 10)
+        return g["dlam"].double().cpu().numpy()
+
+    want = sum(dlam(lo, min(lo + 4, B)) for lo in range(0, B, 4))
+    assert rel_l2(dlam(0, B), want) <= TOL_F32
