@@ -603,8 +603,10 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float va = gt.w[m] * __uint_as_float(x[q] << 16), vb = gt.w[m] * __uint_as_float(x[q] & 0xffff0000u);
-                hi[q] = pack_bf16x2(va, vb);
-                if (SPLIT) lo[q] = pack_bf16x2(va - __uint_as_float(hi[q] << 16), vb - __uint_as_float(hi[q] & 0xffff0000u));
+                if (SPLIT)
+                    split2(va, vb, hi[q], lo[q]);
+                else
+                    hi[q] = pack_bf16x2(va, vb);
             }
             *reinterpret_cast<uint4*>(tile_piece<DK>(sAh[b], i / PK, i % PK)) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
             if (SPLIT) *reinterpret_cast<uint4*>(tile_piece<DK>(sAl[b], i / PK, i % PK)) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
