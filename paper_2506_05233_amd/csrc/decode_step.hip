@@ -258,11 +258,11 @@ __global__ __launch_bounds__(DK) __attribute__((amdgpu_waves_per_eu(3))) void de
 {
     decode_step<Tin, DK, DV, PACKED, kKeep>(a);
 }
-// the same with non-temporal state traffic
-template <typename Tin, int DK, int DV, bool PACKED>
+// the same with non-temporal state traffic, for packed states
+template <typename Tin, int DK, int DV>
 __global__ __launch_bounds__(DK) __attribute__((amdgpu_waves_per_eu(3))) void decode_stream_kernel(DecodeArgs a)
 {
-    decode_step<Tin, DK, DV, PACKED, kStream>(a);
+    decode_step<Tin, DK, DV, true, kStream>(a);
 }
 
 // Few pairs (see launch_dk): the step is then one chain of dependent products, and the kernel
@@ -501,14 +501,19 @@ hipError_t launch_dk(const DecodeArgs& a, hipStream_t stream)
             hipLaunchKernelGGL((decode_few_kernel<Tin, DK, 128, PACKED>), dim3(blocks), dim3(DK * 4), 0, stream, a);
         return hipGetLastError();
     }
-    // States that outgrow the 256 MB last-level cache are streamed past the caches, which the
-    // next step would find holding other pairs anyway (us per step, streamed against kept: 4096
-    // pairs d 128 213.5 / 217.5, packed 171 / 184, d 128 x 64 164 / 167; within the cache it
-    // costs: 1024 pairs d 128 58.0 / 53.9, 4096 of d 64 57.7 / 55.1).
-    const int64_t bytes = int64_t(blocks) * DK * ((PACKED ? DK / 2 + 1 : DK) + a.d_v) * 4;
-    const bool big = bytes > (int64_t(256) << 20);
-    auto kern = a.d_v == 64 ? (big ? decode_stream_kernel<Tin, DK, 64, PACKED> : decode_step_kernel<Tin, DK, 64, PACKED>)
-                            : (big ? decode_stream_kernel<Tin, DK, 128, PACKED> : decode_step_kernel<Tin, DK, 128, PACKED>);
+    auto kern = a.d_v == 64 ? decode_step_kernel<Tin, DK, 64, PACKED> : decode_step_kernel<Tin, DK, 128, PACKED>;
+    // Packed states well above the 256 MB last-level cache are streamed past the caches, which
+    // the next step would find holding other pairs anyway (us per step over several states in
+    // turn, streamed against kept: 4096 pairs d 128, 405 MB, 174 / 184, and stepping one state
+    // over and over 174 / 183).  Nearer the cache's size a state stepped over and over is partly
+    // found there (d 128 x 64, 270 MB: 132 / 127, several in turn 128 / 139), within it wholly.
+    // Full states are kept: streamed, several in turn take 209 for 217, but the first step
+    // after a state was written takes 255 for 225 (packed 195 both).
+    if constexpr (PACKED) {
+        const int64_t bytes = int64_t(blocks) * DK * (DK / 2 + 1 + a.d_v) * 4;
+        if (bytes > (int64_t(384) << 20))
+            kern = a.d_v == 64 ? decode_stream_kernel<Tin, DK, 64> : decode_stream_kernel<Tin, DK, 128>;
+    }
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(DK), 0, stream, a);
     return hipGetLastError();
 }
