@@ -172,11 +172,15 @@ int mesa_forward_ex(const void* q, const void* k, const void* v, const float* ga
  * final_G.  `precision` must be the one the following mesa_forward_solve
  * uses: it selects the workspace layout (fp32 states for MESA_PREC_F32,
  * bf16 states laid out as matrix-core operands for MESA_PREC_BF16).
- * One kernel launch, or two on the bf16 path when batch x heads is too small
- * to occupy the GPU (at most 64 sequences): the chunks are then cut into
+ * One kernel launch, or two when batch x heads is too small to occupy the GPU:
+ * on the bf16 path (at most 64 sequences) the chunks are then cut into
  * segments whose totals a first launch computes from a zero state, and the
  * second walks every segment from the state entering it (the chunk recurrence
- * of App. D applied to whole segments), with the unused half of the workspace
+ * of App. D applied to whole segments); where the states are few enough, on
+ * either path at chunk 64, the first launch computes every chunk's total side
+ * by side and the second scans them into the entering states; with only the
+ * final states asked for, the second adds the segments' totals.  The unused
+ * part of the workspace serves
  * as scratch for the totals. */
 int mesa_forward_states(const void* k, const void* v, const float* gamma, const float* beta,
                         int64_t batch, int64_t heads, int64_t seq_len, int64_t d_k, int64_t d_v,
@@ -368,7 +372,8 @@ size_t mesa_backward_workspace_bytes(int64_t batch, int64_t heads, int64_t seq_l
  * Chunk states, adjoints and every gradient sum are fp32; the solve follows
  * `precision`.  Outputs must overlap neither an input nor each other
  * (MESA_ERR_ARG).  seq_len 0 writes dlambda = 0 only.  Six kernel launches on
- * `stream` (seven on the bf16 route). */
+ * `stream`, and one more for each of the two scans (chunk states, adjoints) that
+ * few sequences split over segments or chunks. */
 int mesa_backward(const void* k, const void* v, const float* gamma, const float* beta,
                   const float* lambda, int64_t batch, int64_t heads, int64_t seq_len, int64_t d_k,
                   int64_t d_v, int dtype, int n_cg, int precision, const float* qstar,

@@ -17,8 +17,9 @@
 // The decay on the carried state (zeta_j) is the reading under which the
 // chunkwise form equals the recurrence; App. D's compact equations omit it.
 //
-// This is the fp32 path: every product is exact fp32 (results agree with fp64 to
-// about 1e-6).  Chunk 64 runs on the matrix cores (chunk_cg_f32_mma_kernel below);
+// This is the fp32 path: products to fp32 accuracy (results agree with fp64 to about 1e-6).
+// Chunk 64 runs on the matrix cores (d_k = 64 in chunk_cg_f32_split.hip, d_k = 128 in
+// chunk_cg_f32_mma_kernel below);
 // chunks 16 and 32 use fp32 FMAs with operands staged in LDS: matrices over the
 // chunk are held as [feature a][token j]; thread t owns column j = t % C and rows
 // a = t / C + (256 / C) m, so the per-column CG scalars reduce over 256 / C threads.

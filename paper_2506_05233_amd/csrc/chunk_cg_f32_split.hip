@@ -28,6 +28,12 @@
 // products per wave and iteration, against up to 192 of four times the length in fp32 form
 // (whose causal sum runs over all earlier tokens of the chunk).  Contractions over the 16
 // tokens of a sub-chunk fill a 32-long one with two of the six terms side by side.
+//
+// Bound by the vector work of the splits and the serial chain of an iteration; the keys' parts
+// stay in LDS so that two workgroups share a compute unit (in registers: 305 of them, one
+// workgroup, 141 us where this takes 100).  Solve, 15 iterations, in fp32 form and here: B4 H8
+// T2048 217 and 100 us, B1 H2 T256 (eight workgroups) 52 and 27 us; error against 64 bits
+// 2.9e-7 and 2.6e-7.
 #include "mesa_device.hpp"
 #include "mesa_kernels.hpp"
 #include "mesa_mfma.hpp"
