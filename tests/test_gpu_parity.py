@@ -794,3 +794,23 @@ def test_chunk_states_from_totals_and_scan(bh, T, dtype, prec, dk, dv):
     ref = oracle.forward(x["q"], x["k"], x["v"], x["gamma"], x["beta"], x["lam"], 8)["out"]
     tol = TOL_BF16 if prec == L.MESA_PREC_BF16 else 2e-6 if dtype == "f32" else TOL_F32
     assert rel_l2(got, ref) <= tol
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_packed_states_streamed_match_kept(dk, dv):
+    """Packed states just above 384 MB take the streaming kernel, the two halves of the same pairs
+    the one that goes through the caches: outputs and states agree bit for bit."""
+    n = (384 << 20) // (dk * (dk // 2 + 1 + dv) * 4) + 1
+    g = torch.Generator(device="cuda").manual_seed(dk + dv)
+    q, k, v = (torch.randn((n, 1, d), generator=g, device="cuda") for d in (dk, dk, dv))
+    q, k = q / q.norm(dim=-1, keepdim=True), k / k.norm(dim=-1, keepdim=True)
+    gam, bet = (torch.rand((n, 1), generator=g, device="cuda") for _ in range(2))
+    lam = torch.rand((1, dk), generator=g, device="cuda") * 0.75 + 0.25
+    H = L.pack_state(torch.diag_embed(torch.rand((n, 1, dk), generator=g, device="cuda")))
+    G = torch.randn((n, 1, dv, dk), generator=g, device="cuda")
+    Hh, Gh = H.clone(), G.clone()
+    out = L.decode_step(H, G, q, k, v, gam, bet, lam, 4, packed=True)
+    for sl in (slice(0, n // 2), slice(n // 2, n)):
+        o = L.decode_step(Hh[sl], Gh[sl], q[sl], k[sl], v[sl], gam[sl], bet[sl], lam, 4, packed=True)
+        assert torch.equal(o, out[sl])
+    assert torch.equal(H, Hh) and torch.equal(G, Gh)
