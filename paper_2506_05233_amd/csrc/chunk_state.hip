@@ -447,17 +447,20 @@ __device__ __forceinline__ bf16x8 tile_col_frag(uint16_t* tile, int t, int u, in
 // (d_k x d_v), both as [key feature R][column c] -- in registers, and walk its chunks
 // in order:
 //
-//   X_{next} = D X + (w ⊙ K)^T Y,   Y = K (part 0) or V (part 1), w_i = beta_i zeta_{end,i}.
+//   X_{next} = D X + K^T (w ⊙ Y),   Y = K (part 0) or V (part 1), w_i = beta_i zeta_{end,i}.
 //
 // With d_k = d_v and single products each workgroup owns half of the columns of both
 // parts, so both read the same bytes (k and half of v) and write the same share of the
 // states; otherwise one workgroup owns H and the other G^T.
 //
-// When fp32 states leave the kernel (the final states), w ⊙ K is split into bf16
+// When fp32 states leave the kernel (the final states), w ⊙ Y is split into bf16
 // high and low parts (two products, ~16-bit weights, states fp32-accurate); when
 // only the bf16 chunk states are produced, the high part alone is used: its
 // rounding (2^-9 per term, averaged over the chunk's 64 terms) stays well below the
-// bf16 rounding of the stored states.
+// bf16 rounding of the stored states.  Totals and states-only walks (split, no chunk states)
+// put the weights on the keys instead, which saves two of ten operand reads: 64 sequences of
+// 4001 tokens, d 128, 64.2 us with the weighted y, 62.4 so.  The walks that store chunk states
+// are bound by the stores and gain nothing from it (B8 H16 T2048 d 128 forward 751 / 755).
 // Eight waves (two per SIMD, so one hides the other's latencies); wave w owns key
 // rows 32 (w % NS) .. +31 (NS = d_k / 32) and a 1/CS share of the columns
 // (CS = 8 / NS); its 16x16 result tiles pair up into complete bf16 A-fragments of
@@ -526,9 +529,10 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
     const int g = lane / 16, ln = lane % 16;
 
     constexpr int DM = DK > DV ? DK : DV;
-    __shared__ __attribute__((aligned(16))) uint16_t sAh[2][C * DK];               // hi(w_i k_i)
-    __shared__ __attribute__((aligned(16))) uint16_t sAl[2][SPLIT ? C * DK : 8];   // lo(w_i k_i)
-    __shared__ __attribute__((aligned(16))) uint16_t sB[2][C * DM];                // y_i
+    constexpr bool WK = SPLIT && !STORE;    // the weights are on the keys, else on y
+    constexpr int PA = WK ? 2 : 1, PB = SPLIT && !WK ? 2 : 1;  // planes: the weighted operand has hi and lo
+    __shared__ __attribute__((aligned(16))) uint16_t sA[2][PA][C * DK];  // k_i, or w_i k_i
+    __shared__ __attribute__((aligned(16))) uint16_t sB[2][PB][C * DM];  // w_i y_i, or y_i
 
     auto run = [&](auto nc_tag) {
         constexpr int NC = decltype(nc_tag)::value;  // columns of this workgroup
@@ -577,10 +581,11 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
         };
         // Staging of a chunk into buffer b, in pieces that the chunk loop interleaves with the
         // previous chunk's products: the gate scan (weights w_i = beta_i zeta_{end,i} of this
-        // thread's tokens, zero past the end, and the chunk decay D), the weighted keys split into
-        // bf16 high and low parts, and y as it is.
+        // thread's tokens, zero past the end, and the chunk decay D), the plain operand as it is,
+        // and the weighted one split into bf16 high and low parts.
+        constexpr int NW = WK ? NK : NY, PW = WK ? PK : PY;
         struct Gate {
-            float w[NK], D;
+            float w[NW], D;
         };
         auto gates = [&](const Regs& R) -> Gate {
             const bool live = lane < R.valid;
@@ -592,13 +597,30 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             const float wl = live ? R.bet * (zlE > lane ? 0.0f : expf(lgE - lg)) : 0.0f;
             Gate gt;
 #pragma unroll
-            for (int m = 0; m < NK; ++m) gt.w[m] = shfl_lane(wl, (tid + m * kWideThreads) / PK);
+            for (int m = 0; m < NW; ++m) gt.w[m] = shfl_lane(wl, (tid + m * kWideThreads) / PW);
             gt.D = zlE >= 0 ? 0.0f : expf(lgE);
             return gt;
         };
-        auto stage_k = [&](const Regs& R, int b, const Gate& gt, int m) {
+        // where y is k, its pieces are the k pieces (the tiles are then equally wide)
+        auto y_piece = [&](const Regs& R, int m) -> uint4 {
+            return (m < NK && y_from_k(8 * ((tid + m * kWideThreads) % PY))) ? R.k[m < NK ? m : 0] : R.y[m];
+        };
+        auto stage_plain = [&](const Regs& R, int b) {
+#pragma unroll
+            for (int m = 0; m < (WK ? NY : NK); ++m) {
+                const int i = tid + m * kWideThreads;
+                if constexpr (WK)
+                    *reinterpret_cast<uint4*>(tile_piece<NC>(sB[b][0], i / PY, i % PY)) = y_piece(R, m);
+                else
+                    *reinterpret_cast<uint4*>(tile_piece<DK>(sA[b][0], i / PK, i % PK)) = R.k[m];
+            }
+        };
+        auto stage_weighted = [&](const Regs& R, int b, const Gate& gt, int m) {
             const int i = tid + m * kWideThreads;
-            const uint32_t x[4] = {R.k[m].x, R.k[m].y, R.k[m].z, R.k[m].w};
+            uint4 piece;
+            if constexpr (WK) piece = R.k[m];
+            else piece = y_piece(R, m);
+            const uint32_t x[4] = {piece.x, piece.y, piece.z, piece.w};
             uint32_t hi[4], lo[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -608,17 +630,14 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
                 else
                     hi[q] = pack_bf16x2(va, vb);
             }
-            *reinterpret_cast<uint4*>(tile_piece<DK>(sAh[b], i / PK, i % PK)) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-            if (SPLIT) *reinterpret_cast<uint4*>(tile_piece<DK>(sAl[b], i / PK, i % PK)) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-        };
-        auto stage_y = [&](const Regs& R, int b) {
-#pragma unroll
-            for (int m = 0; m < NY; ++m) {
-                const int i = tid + m * kWideThreads;
-                // where y is k, its pieces are the k pieces (the tiles are then equally wide)
-                const uint4 y = (m < NK && y_from_k(8 * (i % PY))) ? R.k[m < NK ? m : 0] : R.y[m];
-                *reinterpret_cast<uint4*>(tile_piece<NC>(sB[b], i / PY, i % PY)) = y;
-            }
+            auto put = [&](int plane, const uint32_t (&u)[4]) {
+                uint16_t* dst;
+                if constexpr (WK) dst = tile_piece<DK>(sA[b][plane], i / PK, i % PK);
+                else dst = tile_piece<NC>(sB[b][plane], i / PY, i % PY);
+                *reinterpret_cast<uint4*>(dst) = make_uint4(u[0], u[1], u[2], u[3]);
+            };
+            put(0, hi);
+            if constexpr (SPLIT) put(1, lo);
         };
 
         f32x4 acc[2][NCT];
@@ -637,7 +656,7 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             return part ? c * DK + R : R * DK + c;
         };
 
-        // chunk n: its state is stored, then acc = D acc + (w ⊙ K)^T Y from buffer n % 2;
+        // chunk n: its state is stored, then acc = D acc + K^T (w ⊙ Y) from buffer n % 2;
         // chunk n + 1 is staged (from Rn1) into the other buffer and chunk n + 3 loaded
         float dprod = 1.0f;  // decay across the chunks walked so far
         auto consume = [&](int n, float D, Regs& Rn1, Regs& Rfree, float& Dnext) {
@@ -693,39 +712,43 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
                 for (int ct = 0; ct < NCT; ++ct) acc[rt][ct] *= D;
-            // every operand of this chunk's products is read from LDS first; the products then
+            // the operands of this chunk's products are read from LDS first; the products then
             // run in three batches with the staging pieces of the next chunk (into the other
             // buffer) between them, and scheduling barriers keep that order
-            bf16x8 ah[C / 32][2], al[C / 32][2], bf[C / 32][NCT];
+            bf16x8 af[PA][C / 32][2], yf[PB][C / 32][NCT];
+            auto operands = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < C / 32; ++u) {
+                for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-                for (int rt = 0; rt < 2; ++rt) {
-                    ah[u][rt] = tile_col_frag<DK>(sAh[b], 2 * sblk + rt, u, g, ln);
-                    if (SPLIT) al[u][rt] = tile_col_frag<DK>(sAl[b], 2 * sblk + rt, u, g, ln);
-                }
+                    for (int pl = 0; pl < PA; ++pl) af[pl][u][rt] = tile_col_frag<DK>(sA[b][pl], 2 * sblk + rt, u, g, ln);
 #pragma unroll
-                for (int ct = 0; ct < NCT; ++ct) bf[u][ct] = tile_col_frag<NC>(sB[b], lct0 + ct, u, g, ln);
-            }
+                for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+                    for (int pl = 0; pl < PB; ++pl) yf[pl][u][ct] = tile_col_frag<NC>(sB[b][pl], lct0 + ct, u, g, ln);
+            };
+            static_assert(C / 32 == 2, "two contraction steps");
+            operands(0);
+            if (!PLAIN) operands(1);
             auto products = [&](int u, int ct_lo, int ct_hi) {
 #pragma unroll
                 for (int ct = ct_lo; ct < ct_hi; ++ct)
 #pragma unroll
                     for (int rt = 0; rt < 2; ++rt) {
-                        acc[rt][ct] = mfma16(ah[u][rt], bf[u][ct], acc[rt][ct]);
-                        if (SPLIT) acc[rt][ct] = mfma16(al[u][rt], bf[u][ct], acc[rt][ct]);
+                        acc[rt][ct] = mfma16(af[0][u][rt], yf[0][u][ct], acc[rt][ct]);
+                        if (SPLIT) acc[rt][ct] = mfma16(af[PA - 1][u][rt], yf[PB - 1][u][ct], acc[rt][ct]);
                     }
             };
             const int bn = (n - nbeg + 1) % 2;  // a chunk past the end stages into a buffer nobody reads
             products(0, 0, NCT);
+            if (PLAIN) operands(1);  // earlier, its operands spill
             const Gate gt = gates(Rn1);
             __builtin_amdgcn_sched_barrier(0);
             products(1, 0, NCT / 2);
-            stage_y(Rn1, bn);
-            stage_k(Rn1, bn, gt, 0);
+            stage_plain(Rn1, bn);
+            stage_weighted(Rn1, bn, gt, 0);
             __builtin_amdgcn_sched_barrier(0);
             products(1, NCT / 2, NCT);
-            if (NK > 1) stage_k(Rn1, bn, gt, NK - 1);
+            if (NW > 1) stage_weighted(Rn1, bn, gt, NW - 1);
             Dnext = gt.D;
             if (PLAIN) load(min(n + 3, nend - 1), Rfree);  // earlier, its addresses spill
             __syncthreads();
@@ -773,8 +796,8 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
         {
             const Gate gt = gates(R0);
 #pragma unroll
-            for (int m = 0; m < NK; ++m) stage_k(R0, 0, gt, m);
-            stage_y(R0, 0);
+            for (int m = 0; m < NW; ++m) stage_weighted(R0, 0, gt, m);
+            stage_plain(R0, 0);
             D0 = gt.D;
         }
         __syncthreads();

@@ -1,0 +1,66 @@
+"""Values near the ends of fp32 and values that are not finite: where they may and may not show."""
+import numpy as np
+import pytest
+
+from paper_2506_05233_amd import libmesa as L
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    L.load()
+    yield
+    torch.cuda.synchronize()
+
+
+def _bf16(x):
+    """fp32 array rounded to the nearest bf16 (ties to even), as fp32."""
+    u = np.ascontiguousarray(x, dtype=np.float32).view(np.uint32)
+    return ((u + 0x7fff + ((u >> 16) & 1)) & 0xffff0000).astype(np.uint32).view(np.float32)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_single_pass_states_round_the_weighted_y(d):
+    """The single-pass bf16 chunk states are sums of k_i[R] bf16(w_i y_i[c]) with y the key (H) or the
+    value (G), rounded to bf16 once.  With one gated token in a chunk the sum is one product of two
+    bf16 numbers, exact in fp32, so every stored bit is known: (w, k, y) whose rounding differs if
+    the weight goes to the key instead (about a third of the elements) must show it nowhere."""
+    T, n = 65, 3
+    rng = np.random.default_rng(d)
+    k, v = (_bf16(rng.standard_normal((n, T, d))) for _ in range(2))
+    beta = np.zeros((n, T), dtype=np.float32)
+    at = [0, 37, 63]
+    w = np.array([0.7, 0.3, 0.9], dtype=np.float32)
+    for b in range(n):
+        beta[b, at[b]] = w[b]
+
+    def dev(x, *shape, dtype=torch.float32):
+        return torch.from_numpy(np.ascontiguousarray(x)).cuda().to(dtype).reshape(*shape)
+
+    kt, vt = (dev(x, n, 1, T, d, dtype=torch.bfloat16) for x in (k, v))
+    gamma, bt = torch.ones((n, 1, T), device="cuda"), dev(beta, n, 1, T)
+    need = L.forward_workspace_bytes(n, 1, T, d, d, 64)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    st = L.load().mesa_forward_states(L._ptr(kt), L._ptr(vt), L._ptr(gamma), L._ptr(bt), n, 1, T, d, d,
+                                      L.MESA_DTYPE_BF16, 64, L.MESA_PREC_BF16, None, None, L._ptr(ws), need,
+                                      L._stream(ws.device))
+    assert st == L.MESA_OK
+    torch.cuda.synchronize()
+    elems = n * 2 * d * d
+    raw = ws.cpu().numpy()[:4 * elems].view(np.uint16).astype(np.uint32) << 16
+    frags = raw.view(np.float32).reshape(2, n, 2, d // 16, d // 32, 4, 16, 2, 4)  # part, bh, chunk, t, sb, g, m, half, i
+    # fragment (t, sb), lane (g, m): rows 32 sb + 16 half + 4 g + i of column 16 t + m
+    got = frags.transpose(0, 1, 2, 4, 7, 5, 8, 3, 6).reshape(2, n, 2, d, d)
+    assert not got[:, :, 0].any()
+    for b in range(n):
+        kb, vb = k[b, at[b]], v[b, at[b]]
+        for part, y in ((0, kb), (1, vb)):
+            want = _bf16(kb[:, None] * _bf16(w[b] * y)[None, :])
+            other = _bf16(_bf16(w[b] * kb)[:, None] * y[None, :])
+            assert (want != other).mean() > 0.1
+            assert np.array_equal(got[part, b, 1], want), (part, b)

@@ -22,12 +22,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Kernels whose small spills were measured and left: (name pattern, maximum scratch bytes
 # per lane).  The split-operand CG keeps one or two values of its chunk set-up in a spill
-# slot (reloaded once per chunk, outside the CG loop); the state scan's fp32-plain-state
-# variant (the backward's state pass) spills a few values that are reloaded off its
-# critical path (removing them by other address forms made the kernel slower).
+# slot (reloaded once per chunk, outside the CG loop).
 KNOWN_SPILLS = [
     (r"chunk_cg_x3_kernel<128, (64|128), true>", 16),
-    (r"chunk_state_wide_kernel<128, (64|128), true, true, true, false>", 48),
 ]
 
 
