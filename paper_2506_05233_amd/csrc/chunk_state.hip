@@ -15,6 +15,7 @@
 #include "mesa_device.hpp"
 #include "mesa_kernels.hpp"
 #include "mesa_mfma.hpp"
+#include "scan_plan.hpp"
 
 namespace mesa {
 namespace {
@@ -489,8 +490,7 @@ constexpr int kWideThreads = 512;  // eight waves: two per SIMD
 struct SegPlan {
     int len;      // chunks per segment (the last may be shorter)
     int total;    // segments of a sequence
-    int first;    // first segment this launch walks
-    int count;    // segments this launch walks, per (sequence, part)
+    int count;    // segments this launch walks, per (sequence, part): the first ones
     bool totals;  // write T_s and D_s (first launch) instead of chunk and final states
     int slots;    // segment totals kept per sequence: total - 1, or total when all are combined
     float* tot;   // [B*H, slots, d_k (d_k + d_v)]: T_s of H, then of G (register order, see seg_total)
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
     // owns H and half 1 owns G^T.  (The split-product variants ran 22-28% slower balanced.)
     constexpr bool BAL = DK == DV && !SPLIT;
     const int half = blk % 2;
-    const int seg = sg.first + (blk / 2) % sg.count;
+    const int seg = (blk / 2) % sg.count;
     const int64_t bh = blk / 2 / sg.count;
     const int nbeg = seg * sg.len, nend = min(nbeg + sg.len, s.n_chunks);  // this segment's chunks
     const int tid = threadIdx.x;
@@ -1043,41 +1043,6 @@ hipError_t launch_scan(const StateArgs& a, int64_t part2, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Segments of the wide scan for bh sequences of n_chunks chunks: doubled while the
-// (sequence, part, segment) workgroups still fit the compute units once (the kernel's
-// LDS allows one workgroup per unit) and each segment keeps at least kMinSegChunks
-// chunks, so the extra totals launch stays small next to the walk it shortens.
-constexpr int kComputeUnits = 256;
-constexpr int kMinSegChunks = 8;
-int wide_segments(int64_t bh, int n_chunks)
-{
-    int S = 1;
-    while (2 * bh * (2 * S) <= kComputeUnits && n_chunks / (2 * S) >= kMinSegChunks) S *= 2;
-    return S;
-}
-
-// Segments of a states-only scan, whose segments all run side by side in one launch (no
-// second walk: their totals are the result but for the combination).  The launch takes
-// ceil(workgroups / compute units) rounds of len chunks; S minimises that, with the
-// combination counted as kCombineChunks chunks of walk (~2 us each) when there is one, and a
-// chunk's worth per 16 segments it reads.  A segment keeps at least two chunks, so that the
-// totals fit the half workspace a states-only call has.
-constexpr int kCombineChunks = 4;
-int final_segments(int64_t bh, int n_chunks)
-{
-    int best = 1;
-    int64_t cost = int64_t(n_chunks) * ((2 * bh + kComputeUnits - 1) / kComputeUnits);
-    for (int S = 2; S <= 128 && n_chunks / S >= 2; ++S) {
-        const int len = (n_chunks + S - 1) / S;
-        const int64_t c = int64_t(len) * ((2 * bh * S + kComputeUnits - 1) / kComputeUnits) + kCombineChunks + S / 16;
-        if (c < cost) {
-            cost = c;
-            best = S;
-        }
-    }
-    return best;
-}
-
 template <int DK, int DV, bool STORE, bool SPLIT, bool PLAIN = false, bool X3 = false>
 void launch_wide_kernel(const StateArgs& a, const SegPlan& sg, int64_t bh, hipStream_t stream)
 {
@@ -1092,17 +1057,16 @@ hipError_t launch_wide(const StateArgs& a, hipStream_t stream)
     const int nc = a.s.n_chunks;
     const bool fin = a.final_H != nullptr || a.final_G != nullptr;
     const bool final_only = !a.store_chunks;
-    int S = final_only ? final_segments(bh, nc) : wide_segments(bh, nc);
-    int len = (nc + S - 1) / S;
-    S = (nc + len - 1) / len;
-    const int slots = final_only ? S : S - 1;
-    const int64_t tot_elems = bh * slots * int64_t(DK) * (DK + DV);
-    const size_t need = size_t(tot_elems + bh * S) * sizeof(float);
-    if (S > 1 && (a.seg_ws == nullptr || a.seg_bytes < need)) {
+    constexpr int64_t kElems = int64_t(DK) * (DK + DV);
+    const size_t scratch = a.seg_ws ? a.seg_bytes : 0;
+    int len = final_only ? final_segment_len(bh, nc, DK, DV, scratch) : int(ceil_div(nc, wide_segments(bh, nc)));
+    int S = int(ceil_div(nc, len));
+    if (!final_only && S > 1 && segment_bytes(bh, S - 1, S, kElems) > scratch) {
         S = 1;
         len = nc;
     }
-    SegPlan sg{len, S, 0, S, false, slots, a.seg_ws, S > 1 ? a.seg_ws + tot_elems : nullptr, 0, 0};
+    const int slots = final_only ? S : S - 1;
+    SegPlan sg{len, S, S, false, slots, a.seg_ws, S > 1 ? a.seg_ws + bh * slots * kElems : nullptr, 0, 0};
     // Few, short sequences: the walk is a chain of chunk steps that leaves most of the chip idle
     // (its segments too: they keep at least kMinSegChunks chunks and the walk runs twice).  The
     // chunks' own totals side by side and one scan over them replace the chain by the rounds
@@ -1122,7 +1086,7 @@ hipError_t launch_wide(const StateArgs& a, hipStream_t stream)
         // the workspace
         const int64_t part2 = a.x3 ? g_plane : mode == kScanFrag ? reinterpret_cast<char*>(a.seg_ws) - static_cast<char*>(a.Hs) : 0;
         if (mode != kScanFrag || (a.seg_ws && a.seg_bytes >= size_t(bh * nc * int64_t(DK) * (DK + DV) * 2))) {
-            const SegPlan p1{1, nc, 0, nc - 1, true, 0, nullptr, nullptr, mode, part2};
+            const SegPlan p1{1, nc, nc - 1, true, 0, nullptr, nullptr, mode, part2};
             launch_wide_kernel<DK, DV, false, true>(a, p1, bh, stream);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;

@@ -298,9 +298,12 @@ int launch_states(const FwdCall& c, bool store_chunks, hipStream_t s)
                        store_chunks ? ws_H(c) : nullptr, store_chunks ? ws_G(c) : nullptr,
                        c.final_H, c.final_G, store_chunks, frag};
     sa.x3 = store_chunks && resolve_precision(c) == MESA_PREC_BF16X3;
-    // The bf16 chunk states fill half of the workspace (and a states-only call none
-    // of it): the other half is scratch for the segmented scan of few sequences.
-    if (c.workspace && (frag || !store_chunks)) {
+    // Scratch for the segmented scan of few sequences: all of the workspace in a states-only
+    // call, else the half that the bf16 chunk states leave.
+    if (c.workspace && !store_chunks) {
+        sa.seg_ws = static_cast<float*>(const_cast<void*>(c.workspace));
+        sa.seg_bytes = mesa_forward_workspace_bytes(c.batch, c.heads, c.seq_len, c.d_k, c.d_v, c.chunk);
+    } else if (c.workspace && frag) {
         const size_t full = mesa_forward_workspace_bytes(c.batch, c.heads, c.seq_len, c.d_k, c.d_v, c.chunk);
         sa.seg_ws = reinterpret_cast<float*>(static_cast<char*>(const_cast<void*>(c.workspace)) + full / 2);
         sa.seg_bytes = full - full / 2;

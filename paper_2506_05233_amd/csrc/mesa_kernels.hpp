@@ -37,8 +37,10 @@ struct StateArgs {
     float* final_G;
     bool store_chunks;
     bool frag;
-    // Scratch for the segmented scan (may be null: then one segment): fp32
-    // segment totals and decays, seg_bytes bytes.  Used by the bf16 scan only.
+    // Scratch for the scan of few sequences (may be null: then one segment), seg_bytes
+    // bytes: the fp32 totals and decays of its segments, or, where every chunk's total
+    // stands at a bf16 fragment state's place, the second half of each.  Used by the
+    // bf16 scan only.
     float* seg_ws = nullptr;
     size_t seg_bytes = 0;
     // With frag: also the same chunk states as plain fp32 (layout of frag == false), from

@@ -1,0 +1,68 @@
+// Which launches a state scan takes, from its sizes alone (host code; no GPU types, so that the
+// rules can be compiled and checked without one).
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+namespace mesa {
+
+constexpr int kComputeUnits = 256;
+
+inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Segments of the wide scan for bh sequences of n_chunks chunks: doubled while the
+// (sequence, part, segment) workgroups still fit the compute units once (the kernel's
+// LDS allows one workgroup per unit) and each segment keeps at least kMinSegChunks
+// chunks, so the extra totals launch stays small next to the walk it shortens.
+constexpr int kMinSegChunks = 8;
+inline int wide_segments(int64_t bh, int n_chunks)
+{
+    int S = 1;
+    while (2 * bh * (2 * S) <= kComputeUnits && n_chunks / (2 * S) >= kMinSegChunks) S *= 2;
+    return S;
+}
+
+// Bytes of `slots` segment totals a sequence (elems floats each) and one decay per segment.
+inline size_t segment_bytes(int64_t bh, int slots, int segments, int64_t elems)
+{
+    return size_t(bh * slots * elems + bh * segments) * sizeof(float);
+}
+
+// Chunks per segment of a states-only scan, whose segments all run side by side in one launch
+// (no second walk: their totals are the result but for the combination); n_chunks = one
+// segment.  Segments shorten the walk while their workgroups find room on the chip (LDS holds
+// one a compute unit at d_k = 128, two or three at 64, which together take four fifths of
+// their times one after the other); from there on they only add totals, which the
+// combination reads back from memory and whose bytes are what limits many sequences.  In ns,
+// fitted to every plan of 187 shapes (1 to 300 sequences, 4 to 1000 chunks, the four pairs of
+// widths; the plan taken is within 14% of the fastest and 5% of one segment), us at d 128: 200
+// sequences of 32 chunks 104 in one segment, 277 in 16; 130 of 64 196 in one, 150 in 3, 369 in
+// 32; 48 of 10 20.7 in one, 22.6 in 2; 4 of 14 25.6 in one, 12.5 in 7.  A segment has at least
+// two chunks, and its total and decay fit the scratch.
+constexpr int kMaxFinalSegments = 128;
+inline int64_t final_cost_ns(int64_t bh, int n_chunks, int d_k, int d_v, int len)
+{
+    const int64_t S = ceil_div(n_chunks, len), elems = int64_t(d_k) * (d_k + d_v), step = 600 + elems * 132 / 4096;
+    const int share = d_k == 128 ? 1 : d_v == 128 ? 2 : 3;  // workgroups a compute unit holds
+    const int64_t each = ceil_div(2 * bh * S, kComputeUnits);
+    const int64_t walk = len * step * (4 * each + ceil_div(each, share)) / 5;
+    return S == 1 ? walk : walk + 3600 + 340 * S + bh * S * elems * 4 / 3100;
+}
+inline int final_segment_len(int64_t bh, int n_chunks, int d_k, int d_v, size_t scratch_bytes)
+{
+    int best = n_chunks;
+    int64_t cost = final_cost_ns(bh, n_chunks, d_k, d_v, best);
+    for (int want = 2; want <= kMaxFinalSegments && n_chunks / want >= 2; ++want) {
+        const int len = int(ceil_div(n_chunks, want)), S = int(ceil_div(n_chunks, len));
+        if (segment_bytes(bh, S, S, int64_t(d_k) * (d_k + d_v)) > scratch_bytes) break;  // S does not fall from here on
+        const int64_t c = final_cost_ns(bh, n_chunks, d_k, d_v, len);
+        if (c < cost) {
+            cost = c;
+            best = len;
+        }
+    }
+    return best;
+}
+
+}  // namespace mesa

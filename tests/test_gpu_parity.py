@@ -259,16 +259,21 @@ def test_segmented_state_scan_matches_oracle(dk, dv):
     assert rel_l2(Gs.cpu().numpy(), G1.cpu().numpy()) <= 1e-6
 
 
-@pytest.mark.parametrize("bh,T", [(1, 64), (1, 3 * 64 + 1), (1, 4 * 64), (2, 23 * 64 + 5), (3, 9 * 64 + 63), (70, 5 * 64 + 1),
-                                  (130, 4 * 64 + 2)])
+@pytest.mark.parametrize("bh,T,segmented", [(1, 64, False), (1, 3 * 64 + 1, False), (1, 4 * 64, False), (2, 23 * 64 + 5, True),
+                                            (3, 9 * 64 + 63, True), (4, 8 * 64, True), (18, 13 * 64 + 1, True),
+                                            (70, 5 * 64 + 1, False), (70, 30 * 64 + 9, True), (130, 4 * 64 + 2, False),
+                                            (130, 31 * 64 + 63, True)])
 @pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
-def test_states_only_scan_combines_all_segments(bh, T, dk, dv):
+def test_states_only_scan_combines_all_segments(bh, T, segmented, dk, dv):
     """States-only call with scratch: every segment's total in one launch, then their
-    combination (one chunk up to many segments, ragged last segments, more sequences than
-    fit the compute units once).  Gates near one keep every segment visible, a zero gate
-    resets memory inside one; the scratch starts as NaN, so a total read before it is written
-    shows.  Final states against the oracle (split-product walk: ~2e-6) and the call without
-    scratch (one walk), 64-bit sums of at most T terms each rounded at 2^-17."""
+    combination (two chunks a segment whose totals and decays a whole workspace just holds, ragged
+    last segments, more sequences than fit the compute units once), or one walk where that
+    is shorter: the scratch starts as NaN, so a total read before it is written shows, and at
+    least two totals a sequence stand in it afterwards exactly where the plan has segments.
+    Gates near one keep every segment visible, a zero gate resets memory inside one.  Final
+    states against the oracle (split-product walk: ~2e-6; the first, the reset and the last
+    sequence) and the call without scratch (one walk), 64-bit sums of at most T terms each
+    rounded at 2^-17."""
     x = W.forward_inputs(bh, 1, T, dk, dv, "bf16", 5.0, seed=T + dk + dv + bh)
     x["gamma"][bh // 2, 0, T // 3] = 0.0
     d = to_device(x, "bf16")
@@ -277,8 +282,11 @@ def test_states_only_scan_combines_all_segments(bh, T, dk, dv):
     Hs, Gs = L.prefill_states(d["k"], d["v"], d["gamma"], d["beta"], workspace=ws)
     H1, G1 = L.prefill_states(d["k"], d["v"], d["gamma"], d["beta"])
     torch.cuda.synchronize()
-    ref = oracle.forward(x["q"], x["k"], x["v"], x["gamma"], x["beta"], x["lam"], 0, want_states=True)
-    assert rel_l2(Hs.cpu().numpy(), ref["H"]) <= 1e-5 and rel_l2(Gs.cpu().numpy(), ref["G"]) <= 1e-5
+    written = int((~torch.isnan(ws)).sum())
+    assert written >= 2 * bh * dk * (dk + dv) if segmented else written == 0
+    at = sorted({0, bh // 2, bh - 1})
+    ref = oracle.forward(x["q"][at], x["k"][at], x["v"][at], x["gamma"][at], x["beta"][at], x["lam"], 0, want_states=True)
+    assert rel_l2(Hs[at].cpu().numpy(), ref["H"]) <= 1e-5 and rel_l2(Gs[at].cpu().numpy(), ref["G"]) <= 1e-5
     assert rel_l2(Hs.cpu().numpy(), H1.cpu().numpy()) <= 1e-6
     assert rel_l2(Gs.cpu().numpy(), G1.cpu().numpy()) <= 1e-6
 
