@@ -914,7 +914,6 @@ __device__ __forceinline__ float wave_prod(float x)
 // One thread per eight elements (a fragment's lane; plain layout: per four) walks the chunks
 // with kAhead chunks' loads in flight, so the walk costs its bytes and not a memory round trip
 // per chunk.  Every workgroup forms the sequence's decays from the gates itself.
-constexpr int kScanChunks = 1024;  // longest sequence (its decays are kept in LDS)
 
 template <int MODE>
 __global__ __launch_bounds__(kThreads) void chunk_scan_kernel(StateArgs a, int64_t part2)
@@ -1067,19 +1066,9 @@ hipError_t launch_wide(const StateArgs& a, hipStream_t stream)
     }
     const int slots = final_only ? S : S - 1;
     SegPlan sg{len, S, S, false, slots, a.seg_ws, S > 1 ? a.seg_ws + bh * slots * kElems : nullptr, 0, 0};
-    // Few, short sequences: the walk is a chain of chunk steps that leaves most of the chip idle
-    // (its segments too: they keep at least kMinSegChunks chunks and the walk runs twice).  The
-    // chunks' own totals side by side and one scan over them replace the chain by the rounds
-    // of the totals, but move the states twice more and add the scan's own chain.  In ns,
-    // fitted to both (us per forward, walk / scan): 4 sequences of 27 chunks d 128 91.4 / 52.4,
-    // 2 of 16 d 64 x 128 45.6 / 28.6, 24 of 16 d 128 x 64 82.3 / 73.3; not 64 of 16 d 128
-    // 134 / 170, 2 of 232 d 64 68.9 / 150, 36 of 10 d 128 71.6 / 78.7.
-    const int64_t step = 600 + int64_t(DK) * (DK + DV) / 20;
-    const int64_t units = (2 * bh * S + kComputeUnits - 1) / kComputeUnits;
-    const int64_t walk_ns = (S > 1 ? 2 * len * step + 5000 : nc * step) * units;
-    const int64_t scan_ns = 6000 + (2 * bh * (nc - 1) + kComputeUnits - 1) / kComputeUnits * step + 450 * nc +
-                            bh * nc * int64_t(DK) * (DK + DV) * 4 / 2700;
-    if (!final_only && !fin && nc > 1 && nc <= kScanChunks && scan_ns < walk_ns) {
+    // few, short sequences: the chunks' own totals and one scan
+    const bool single = a.frag && !a.Hs32;
+    if (!final_only && !fin && wide_takes_scan(single, bh, nc, kElems, S, len)) {
         const int64_t g_plane = bh * nc * int64_t(DV) * DK * 2;
         const int mode = a.x3 ? kScanX3 : a.Hs32 ? kScanBoth : kScanFrag;
         // second halves of the totals: x3 the low plane of G, bf16 fragments the other half of
@@ -1112,8 +1101,7 @@ hipError_t launch_wide(const StateArgs& a, hipStream_t stream)
         SegPlan p1 = sg;
         p1.count = S - 1;
         p1.totals = true;
-        const bool single = a.store_chunks && !a.x3 && a.frag && !a.Hs32 && !fin;
-        if (single)
+        if (a.store_chunks && single && !fin)
             launch_wide_kernel<DK, DV, false, false>(a, p1, bh, stream);
         else
             launch_wide_kernel<DK, DV, false, true>(a, p1, bh, stream);

@@ -65,4 +65,37 @@ inline int final_segment_len(int64_t bh, int n_chunks, int d_k, int d_v, size_t 
     return best;
 }
 
+// The chunk states of few, short sequences from the chunks' own totals, side by side in one
+// launch, and one scan over them, instead of the walk (in `segments` of len chunks each).  The
+// walk is a chain of chunk steps that leaves most of the chip idle (its segments too: they keep
+// at least kMinSegChunks chunks and run twice); the totals are rounds of one step each, but move
+// the states twice more, and the scan is a chain of its own.  Both cost more once the states
+// outgrow the last-level cache (~150 MB written).  In ns, for the walks of split products and of
+// the single one, whose steps are shorter; fitted to both forms at 999 shapes of each (1 to 128
+// sequences, 2 to 1000 chunks, to 537 MB of states) and to 303 of the backward's, where the form
+// taken is within 12% of the faster one.  us of the state
+// pass, walk / scan, d 128 unless given:
+//   split: 4 of 32 38.2 / 33.6, 24 of 20 45.3 / 42.6, 2 of 8 19.4 / 12.3;
+//     not 64 of 13 31.9 / 64.3, 8 of 128 53.7 / 104, 16 of 256 (537 MB) 187 / 456
+//   single: 2 of 32 d 64 18.5 / 12.7, 1 of 109 d 128 x 64 44.0 / 32.5, 2 of 64 33.2 / 26.8;
+//     not 16 of 13 21.6 / 29.2, 12 of 13 21.2 / 26.1, 128 of 32 (537 MB) 83 / 327
+constexpr int kScanChunks = 1024;  // longest sequence scanned (its decays are kept in LDS)
+constexpr int64_t kCacheBytes = 150000000;
+inline int64_t bytes_beyond_cache(int64_t bytes) { return bytes > kCacheBytes ? bytes - kCacheBytes : 0; }
+inline bool wide_takes_scan(bool single, int64_t bh, int n_chunks, int64_t elems, int segments, int len)
+{
+    if (n_chunks < 2 || n_chunks > kScanChunks) return false;
+    const int64_t e = elems / 4096, S = segments, nc = n_chunks;
+    const int64_t units = ceil_div(2 * bh * S, kComputeUnits), rounds = ceil_div(2 * bh * (nc - 1), kComputeUnits);
+    const int64_t bytes = bh * nc * elems * 4, over = bytes_beyond_cache(bytes);
+    if (single) {
+        const int64_t step = 489 + 104 * e;
+        return 4700 + 138 * nc + rounds * step * 82 / 100 + bytes / 2390 + over / 7350 <
+               units * (S > 1 ? 2 * len * step + 2860 + 66 * S * e : nc * step) + over / 11850;
+    }
+    const int64_t step = 615 + 189 * e;
+    return 3500 + nc * (441 + 3 * e) + rounds * step * 9 / 10 + bytes / 2675 + over / 3340 <
+           units * (S > 1 ? 2 * len * step + 1500 + 89 * S * e : nc * step) + over / 7900;
+}
+
 }  // namespace mesa

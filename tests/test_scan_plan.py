@@ -9,6 +9,10 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 WRAPPER = """
 #include "scan_plan.hpp"
 extern "C" int final_len(int64_t bh, int nc, int dk, int dv, size_t bytes) { return mesa::final_segment_len(bh, nc, dk, dv, bytes); }
+extern "C" int wide_scan(int single, int64_t bh, int nc, int64_t elems) {
+  const int S = mesa::wide_segments(bh, nc), len = int(mesa::ceil_div(nc, S));
+  return mesa::wide_takes_scan(single != 0, bh, nc, elems, int(mesa::ceil_div(nc, len)), len);
+}
 """
 
 
@@ -22,6 +26,7 @@ def plan(tmp_path_factory):
     p = ctypes.CDLL(str(lib))
     i64, ci, sz = ctypes.c_int64, ctypes.c_int, ctypes.c_size_t
     p.final_len.argtypes, p.final_len.restype = [i64, ci, ci, ci, sz], ci
+    p.wide_scan.argtypes, p.wide_scan.restype = [ci, i64, ci, i64], ci
     return p
 
 
@@ -69,3 +74,23 @@ def test_states_only_plan_segments_short_prompts(plan):
 def test_states_only_plan_is_decided_as_measured(plan, bh, nc, d, one, more):
     got = plan.final_len(bh, nc, d, d, _workspace(bh, nc, 2 * d * d))
     assert (got == nc) == (one < more), got
+
+
+# bf16 chunk states, us of the state pass by the walk and by totals and scan: (single product, sequences, chunks, d_k, d_v)
+WIDE = [(False, 4, 32, 128, 128, 38.2, 33.6), (False, 24, 20, 128, 128, 45.3, 42.6), (False, 2, 8, 128, 128, 19.4, 12.3),
+        (False, 64, 13, 128, 128, 31.9, 64.3), (False, 8, 128, 128, 128, 53.7, 103.6), (False, 16, 256, 128, 128, 187.3, 455.6),
+        (False, 24, 32, 128, 128, 41.4, 61.7), (False, 1, 1000, 64, 64, 64.0, 300.0), (False, 32, 64, 128, 128, 100.8, 193.6),
+        (True, 2, 32, 64, 64, 18.5, 12.7), (True, 1, 109, 128, 64, 44.0, 32.5), (True, 2, 64, 128, 128, 33.2, 26.8),
+        (True, 16, 13, 128, 128, 21.6, 29.2), (True, 12, 13, 128, 128, 21.2, 26.1), (True, 128, 32, 128, 128, 83.3, 327.1),
+        (True, 8, 256, 128, 128, 66.9, 191.8), (True, 24, 20, 128, 64, 32.9, 35.8)]
+
+
+@pytest.mark.parametrize("single,bh,nc,dk,dv,walk,scan", WIDE)
+def test_bf16_state_form_is_decided_as_measured(plan, single, bh, nc, dk, dv, walk, scan):
+    assert bool(plan.wide_scan(single, bh, nc, dk * (dk + dv))) == (scan < walk)
+
+
+def test_scan_ends_where_its_decays_do(plan):
+    """One chunk has nothing to scan; past 1024 chunks the scan's decays do not fit its LDS."""
+    for single in (0, 1):
+        assert not plan.wide_scan(single, 1, 1, 64 * 128) and not plan.wide_scan(single, 1, 1025, 64 * 128)
