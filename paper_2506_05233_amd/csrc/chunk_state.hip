@@ -1154,13 +1154,7 @@ hipError_t launch_chunk_state(const StateArgs& a, hipStream_t stream)
     if (!a.s.bf16 && a.s.chunk == 64) {
         const unsigned blocks = unsigned(bh * ((a.s.d_k + a.s.d_v) / 16) * (a.s.d_k / 64));
         const int nc = a.s.n_chunks;
-        // the chunks' totals and a scan instead of the walk, as for bf16 inputs (launch_wide; us
-        // per forward, walk / scan: 2 sequences of 232 chunks d 64 223 / 90, 8 of 13 32.1 / 28.1;
-        // not 32 of 32 76.9 / 81.3, 16 of 64 d 128 268 / 309)
-        const int64_t walk_ns = 900 * int64_t(nc) * ((int64_t(blocks) + 511) / 512);
-        const int64_t scan_ns = 6000 + 300 * int64_t(nc) + bh * nc * int64_t(a.s.d_k) * (a.s.d_k + a.s.d_v) * 4 / 2700 +
-                                int64_t(blocks) * (nc - 1);
-        if (a.store_chunks && !a.final_H && !a.final_G && nc > 1 && nc <= kScanChunks && scan_ns < walk_ns) {
+        if (a.store_chunks && !a.final_H && !a.final_G && f32_takes_scan(bh, nc, a.s.d_k, a.s.d_v)) {
             auto one = a.s.d_k == 64 ? chunk_state_f32_kernel<64, 2> : chunk_state_f32_kernel<128, 2>;
             hipLaunchKernelGGL(one, dim3(blocks * unsigned(nc - 1)), dim3(kThreads), 0, stream, a);
             const hipError_t e = hipGetLastError();

@@ -98,4 +98,20 @@ inline bool wide_takes_scan(bool single, int64_t bh, int n_chunks, int64_t elems
            units * (S > 1 ? 2 * len * step + 1500 + 89 * S * e : nc * step) + over / 7900;
 }
 
+// The same choice for fp32 states (chunk 64): `each` workgroups walk side by side on a compute
+// unit, a step of 0.79 us and half a microsecond for every further one.  Fitted to both forms at
+// 999 shapes (to 537 MB) and to 303 of the backward's, where the form taken is within 15% of the
+// faster one, the scan never more than 8% the slower; us of the state pass, walk / scan, d 64
+// unless given: 8 of 13 14.4 / 10.8, 8 of 13 d 64 x 128 14.5 / 12.1, 2 of 256 221 / 54, 24 of 32
+// d 64 x 128 (two a unit) 48.7 / 41.4, 8 of 1000 (262 MB) 865 / 478; not 2 of 8 9.7 / 10.8, 32 of
+// 32 31.8 / 36.6, 16 of 64 d 128 (134 MB) 96 / 133, 24 of 256 (201 MB) 229 / 259.
+inline bool f32_takes_scan(int64_t bh, int n_chunks, int d_k, int d_v)
+{
+    if (n_chunks < 2 || n_chunks > kScanChunks) return false;
+    const int64_t nc = n_chunks, blocks = bh * ((d_k + d_v) / 16) * (d_k / 64), each = ceil_div(blocks, kComputeUnits);
+    const int64_t bytes = bh * nc * d_k * (d_k + d_v) * 4, over = bytes_beyond_cache(bytes);
+    return 5270 + 110 * nc + blocks * (nc - 1) * 184 / 100 + bytes / 3742 + over / 1462 <
+           nc * (788 + 508 * (each - 1)) + over / 5384;
+}
+
 }  // namespace mesa

@@ -13,6 +13,7 @@ extern "C" int wide_scan(int single, int64_t bh, int nc, int64_t elems) {
   const int S = mesa::wide_segments(bh, nc), len = int(mesa::ceil_div(nc, S));
   return mesa::wide_takes_scan(single != 0, bh, nc, elems, int(mesa::ceil_div(nc, len)), len);
 }
+extern "C" int f32_scan(int64_t bh, int nc, int dk, int dv) { return mesa::f32_takes_scan(bh, nc, dk, dv); }
 """
 
 
@@ -27,6 +28,7 @@ def plan(tmp_path_factory):
     i64, ci, sz = ctypes.c_int64, ctypes.c_int, ctypes.c_size_t
     p.final_len.argtypes, p.final_len.restype = [i64, ci, ci, ci, sz], ci
     p.wide_scan.argtypes, p.wide_scan.restype = [ci, i64, ci, i64], ci
+    p.f32_scan.argtypes, p.f32_scan.restype = [i64, ci, ci, ci], ci
     return p
 
 
@@ -90,7 +92,20 @@ def test_bf16_state_form_is_decided_as_measured(plan, single, bh, nc, dk, dv, wa
     assert bool(plan.wide_scan(single, bh, nc, dk * (dk + dv))) == (scan < walk)
 
 
+# fp32 chunk states, the same: (sequences, chunks, d_k, d_v)
+F32 = [(8, 13, 64, 64, 14.4, 10.8), (8, 13, 64, 128, 14.5, 12.1), (2, 256, 64, 64, 221.3, 53.9), (24, 32, 64, 128, 48.7, 41.4), (8, 1000, 64, 64, 864.8, 478.5),
+       (2, 13, 128, 128, 14.4, 11.0), (1, 20, 64, 64, 19.8, 10.6), (12, 109, 128, 64, 152.0, 129.0), (2, 8, 64, 64, 9.8, 10.8),
+       (32, 32, 64, 64, 31.8, 36.6), (16, 64, 128, 128, 96.2, 133.1), (24, 256, 64, 64, 228.5, 259.0), (24, 128, 128, 64, 328.0, 360.8),
+       (8, 512, 128, 64, 454.6, 500.5), (48, 128, 64, 128, 354.0, 377.6)]
+
+
+@pytest.mark.parametrize("bh,nc,dk,dv,walk,scan", F32)
+def test_f32_state_form_is_decided_as_measured(plan, bh, nc, dk, dv, walk, scan):
+    assert bool(plan.f32_scan(bh, nc, dk, dv)) == (scan < walk)
+
+
 def test_scan_ends_where_its_decays_do(plan):
     """One chunk has nothing to scan; past 1024 chunks the scan's decays do not fit its LDS."""
     for single in (0, 1):
         assert not plan.wide_scan(single, 1, 1, 64 * 128) and not plan.wide_scan(single, 1, 1025, 64 * 128)
+    assert not plan.f32_scan(1, 1, 64, 64) and plan.f32_scan(1, 1024, 64, 64) and not plan.f32_scan(1, 1025, 64, 64)
