@@ -64,3 +64,48 @@ def test_single_pass_states_round_the_weighted_y(d):
             other = _bf16(_bf16(w[b] * kb)[:, None] * y[None, :])
             assert (want != other).mean() > 0.1
             assert np.array_equal(got[part, b, 1], want), (part, b)
+
+
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("dk", [64, 128])
+def test_decode_few_pairs_large_curvature(dk, packed):
+    """p^T A p near and past the largest fp32 number: the kernel for few pairs follows the one for many
+    (states aligned to 4 bytes only take that one).  A = s (u u^T + I / 8) with s a power of two: up to
+    overflow every CG quantity scales exactly, the solve ends after two iterations, and the outputs
+    (G scaled by s too) are those of s = 1; past it alpha = delta / inf = 0 leaves the Jacobi start,
+    finite.  The start is up to 8 times the solution and its roundings grow 8 times in the solve (the
+    condition of A): 16 roundings of 2^-24 times 64."""
+    u = (1.0 + 0.1 * np.cos(np.arange(dk))) / np.sqrt(dk)
+    q = u / np.linalg.norm(u) * 0.8  # |q|^2 in [1/2, 2): solved unscaled
+    A = np.outer(u, u) + np.eye(dk) / 8
+    r = q - A @ (q / np.diag(A))
+    top = 126 - int(np.floor(np.log2(r @ A @ r)))  # 2^top p^T A p in [2^126, 2^127)
+    G1 = np.random.default_rng(dk).standard_normal((dk, dk))
+
+    def step(e, aligned):
+        s = 2.0 ** e
+
+        def place(x):
+            x = torch.from_numpy(x.astype(np.float32)).cuda()
+            buf = torch.empty(x.numel() + 4, device="cuda")
+            at = 0 if aligned else 1
+            view = buf[at:at + x.numel()].view(x.shape)
+            view.copy_(x)
+            return view
+        H = torch.from_numpy((s * np.outer(u, u)).astype(np.float32)).cuda().reshape(1, 1, dk, dk)
+        H = (L.pack_state(H) if packed else H).cpu().numpy()
+        z = torch.zeros((1, 1, dk), device="cuda")
+        one = torch.ones((1, 1), device="cuda")
+        out = L.decode_step(place(H), place(s * G1.reshape(1, 1, dk, dk)), torch.from_numpy(q.astype(np.float32)).cuda().reshape(1, 1, dk),
+                            z, z.clone(), one, one.clone(), torch.full((1, dk), s / 8, device="cuda"), 6, packed=packed)
+        torch.cuda.synchronize()
+        return out.double().cpu().numpy()
+
+    for e in (0, top - 2, top, top + 1, top + 4):
+        few, many = step(e, True), step(e, False)
+        assert np.isfinite(many).all(), e
+        assert np.isfinite(few).all(), e
+        assert np.linalg.norm(few - many) <= 6e-5 * np.linalg.norm(many), e
+        if e <= top + 1:
+            want = step(0, False)
+            assert np.linalg.norm(few - want) <= 6e-5 * np.linalg.norm(want), e
