@@ -512,14 +512,14 @@ void chunk_cg_f32_split_kernel(CgArgs a)
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (2 * u > wave) continue;
-            uint16_t* tv = sV;
-            Op3 vf;
-            vf.h = halves(tile_col_half<DV>(tv, mt, 2 * u, g, n), tile_col_half<DV>(tv, mt, 2 * u + 1, g, n));
-            tv += kC * DV;
-            vf.m = halves(tile_col_half<DV>(tv, mt, 2 * u, g, n), tile_col_half<DV>(tv, mt, 2 * u + 1, g, n));
-            tv += kC * DV;
-            vf.l = halves(tile_col_half<DV>(tv, mt, 2 * u, g, n), tile_col_half<DV>(tv, mt, 2 * u + 1, g, n));
-            o = mfma6(vf, so[u], o);
+            // a later sub-chunk's values are masked out, not multiplied by zero: an infinity or a
+            // NaN among them must not reach this sub-chunk's tokens
+            const uint32_t keep = 2 * u + 1 <= wave ? ~0u : 0u;
+            auto pair = [&](uint16_t* tv) __attribute__((always_inline)) -> bf16x8 {
+                const uint2 later = tile_col_half<DV>(tv, mt, 2 * u + 1, g, n);
+                return halves(tile_col_half<DV>(tv, mt, 2 * u, g, n), make_uint2(later.x & keep, later.y & keep));
+            };
+            o = mfma6(Op3{pair(sV), pair(sV + kC * DV), pair(sV + 2 * kC * DV)}, so[u], o);
         }
         if (j < valid) *reinterpret_cast<f32x4*>(a.out + (tok0 + j) * DV + 16 * mt + 4 * g) = o;
     }

@@ -109,3 +109,24 @@ def test_decode_few_pairs_large_curvature(dk, packed):
         if e <= top + 1:
             want = step(0, False)
             assert np.linalg.norm(few - want) <= 6e-5 * np.linalg.norm(want), e
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("dv", [64, 128])
+@pytest.mark.parametrize("tile", [1, 2, 3])
+def test_value_of_a_later_sub_chunk_stays_out_of_earlier_tokens(tile, dv, dtype):
+    """fp32 products, d_k = 64, chunk 64: an infinity or a NaN among the values of one 16-token
+    sub-chunk leaves the outputs of every earlier sub-chunk bit for bit as they were."""
+    g = torch.Generator(device="cuda").manual_seed(tile + dv)
+    n, t = 2, 64
+    q, k, v = (torch.randn((1, n, t, d), generator=g, device="cuda").to(dtype) for d in (64, 64, dv))
+    gamma, beta = (torch.rand((1, n, t), generator=g, device="cuda") for _ in range(2))
+    lam = torch.rand((n, 64), generator=g, device="cuda") + 0.25
+    clean = L.forward(q, k, v, gamma, beta, lam, 8, 64, L.MESA_PREC_F32)
+    v = v.clone()
+    v[0, 0, 16 * tile + 3, 5] = float("nan")
+    v[0, 1, 16 * tile, 7] = float("inf")
+    got = L.forward(q, k, v, gamma, beta, lam, 8, 64, L.MESA_PREC_F32)
+    torch.cuda.synchronize()
+    assert torch.equal(got[:, :, :16 * tile], clean[:, :, :16 * tile])
+    assert not torch.isfinite(got[0, 0, 16 * tile + 3, 5])
