@@ -392,7 +392,7 @@ void chunk_cg_f32_split_kernel(CgArgs a)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int f = 16 * t + 4 * g + e;
-                x[t][e] = qv[t][e] * __builtin_amdgcn_rcpf(zs * sDiag[wave][f] + acc[e] + sLam[f]);
+                x[t][e] = qv[t][e] / (zs * sDiag[wave][f] + acc[e] + sLam[f]);
             }
         }
     }

@@ -130,3 +130,21 @@ def test_value_of_a_later_sub_chunk_stays_out_of_earlier_tokens(tile, dv, dtype)
     torch.cuda.synchronize()
     assert torch.equal(got[:, :, :16 * tile], clean[:, :, :16 * tile])
     assert not torch.isfinite(got[0, 0, 16 * tile + 3, 5])
+
+
+@pytest.mark.parametrize("dk", [64, 128])
+@pytest.mark.parametrize("exponent", [120, 126, 127])
+def test_jacobi_start_divides(dk, exponent):
+    """n_cg = 0, fp32 products: q* = q / diag(H_t + Lambda) also where 1 / diag is below the smallest
+    normal number (the quotient of q scaled to |q| near one keeps 2^-19 there: subnormals of 2^-149
+    beside elements of q / 8)."""
+    t = 70
+    g = torch.Generator(device="cuda").manual_seed(dk + exponent)
+    q = torch.randn((1, 1, t, dk), generator=g, device="cuda") * 2.0 ** 12
+    k, v = (torch.randn((1, 1, t, dk), generator=g, device="cuda") for _ in range(2))
+    gamma, beta = torch.ones((1, 1, t), device="cuda"), torch.zeros((1, 1, t), device="cuda")
+    lam = torch.full((1, dk), 2.0 ** exponent, device="cuda")
+    got = L.forward(q, k, v, gamma, beta, lam, 0, 64, L.MESA_PREC_F32, want_qstar=True)["qstar"]
+    want = q.double() / 2.0 ** exponent
+    torch.cuda.synchronize()
+    assert float((got.double() - want).norm() / want.norm()) <= (1e-7 if exponent == 120 else 2.0 ** -18)
