@@ -2,8 +2,9 @@
 // d_k = 64 and chunk C = 64 (MESA_PREC_F32, and the backward's fp32 solve).
 //
 // An fp32 number has 24 significant bits, three bf16 numbers 8 each: every fp32 operand of a
-// product is carried exactly as x = h + m + l (h = bf16(x), m = bf16(x - h), l = x - h - m),
-// and a product a b as the six terms
+// product is carried exactly as x = h + m + l (h = bf16(x), m = bf16(x - h), l = x - h - m)
+// between 2^-98 and 2^127 (below, l falls under the smallest bf16 number; at the top, h rounds
+// to infinity; see lift_by), and a product a b as the six terms
 //
 //   h_a h_b + (h_a m_b + m_a h_b) + (h_a l_b + l_a h_b + m_a m_b),
 //
@@ -126,6 +127,33 @@ __device__ __forceinline__ f32x4 join3(const Half3& a)
     return r;
 }
 
+// Operands that lie at an end of fp32 are brought into the range that splits exactly by a power of
+// two, which the result gives back: reach 0 stands for numbers all below 2^-60, 2 for some from
+// 2^127 on, 1 for others (the same for every lane of a wave).
+__device__ __forceinline__ float lift_by(int reach) { return reach == 0 ? 0x1p60f : reach == 2 ? 0x1p-60f : 1.0f; }
+__device__ __forceinline__ int reach_of(float largest)
+{
+    return __any(largest >= 0x1p127f) ? 2 : __any(largest >= 0x1p-60f) ? 1 : 0;
+}
+__device__ __forceinline__ float largest4(float m, const f32x4& v)
+{
+    return fmaxf(fmaxf(m, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
+}
+template <int N>
+__device__ __forceinline__ int reach_of(const f32x4 (&v)[N])
+{
+    float t = 0.0f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) t = largest4(t, v[i]);
+    return reach_of(t);
+}
+template <int N>
+__device__ __forceinline__ void scale(f32x4 (&v)[N], float by)
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] *= by;
+}
+
 __device__ __forceinline__ f32x4 load_vec4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 __device__ __forceinline__ f32x4 load_vec4(const bf16_t* p)
 {
@@ -209,6 +237,7 @@ void chunk_cg_f32_split_kernel(CgArgs a)
     __shared__ float sLg[kC], sBeta[kC];
     __shared__ __attribute__((aligned(16))) float sWe[kC];  // beta_i x decay from i to its sub-chunk's last token
     __shared__ int sZl[kC];
+    __shared__ int sReach[kWaves];
     f32x4* sE = reinterpret_cast<f32x4*>(sEV);
     bf16x8* sKL = reinterpret_cast<bf16x8*>(sEV);
     uint16_t* sV = reinterpret_cast<uint16_t*>(sEV);
@@ -384,6 +413,8 @@ void chunk_cg_f32_split_kernel(CgArgs a)
     {
         const float qs = __builtin_ldexpf(1.0f, -qsh);
         const Right16 zb = right16(split3(zw));
+        f32x4 d[MT];
+        float least = INFINITY;
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
             const f32x4 k = join3(kh[t]);
@@ -392,15 +423,25 @@ void chunk_cg_f32_split_kernel(CgArgs a)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int f = 16 * t + 4 * g + e;
-                x[t][e] = qv[t][e] / (zs * sDiag[wave][f] + acc[e] + sLam[f]);
+                d[t][e] = zs * sDiag[wave][f] + acc[e] + sLam[f];
+                least = fminf(least, d[t][e]);
             }
         }
-    }
-    matvec(x, w);
+        // a large system has a small x; CG's other directions are residuals of a unit q
+        const bool large = !__any(least < 0x1p60f);
+        const float up = large ? 0x1p60f : 1.0f, down = large ? 0x1p-60f : 1.0f;
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        r[t] = qv[t] - w[t];
-        p[t] = r[t];
+        for (int t = 0; t < MT; ++t) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[t][e] = up * qv[t][e] / d[t][e];
+            x[t] = down * p[t];
+        }
+        matvec(p, w);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            r[t] = qv[t] - down * w[t];
+            p[t] = r[t];
+        }
     }
     float delta = col_dot(r, r);
     const float thr = a.eps2 * delta;  // Alg. 1: the column stops once |r|^2 <= eps^2 |r_0|^2
@@ -445,28 +486,49 @@ void chunk_cg_f32_split_kernel(CgArgs a)
 
     // ---- read-out o_j = zeta_j G_c x_j + sum_{i<=j} beta_i zeta_{j,i} v_i (k_i . x_j)
     constexpr int kPerV = kC * DV / 8 / kThreads;
-    f32x4 vv[kPerV][2];
+    auto load_v = [&](f32x4 (&vv)[2 * kPerV], int id) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kPerV; ++u) {
-        const int piece = tid + u * kThreads, tok = piece / (DV / 8), c = piece % (DV / 8);
-        const Tin* src = vp + int64_t(min(tok, valid - 1)) * DV + 8 * c;
-        vv[u][0] = load_vec4(src);
-        vv[u][1] = load_vec4(src + 4);
-        if (tok >= valid) vv[u][0] = vv[u][1] = zero4;
-    }
+        for (int u = 0; u < kPerV; ++u) {
+            const int piece = id + u * kThreads, tok = piece / (DV / 8), c = piece % (DV / 8);
+            const Tin* src = vp + int64_t(min(tok, valid - 1)) * DV + 8 * c;
+            vv[2 * u] = load_vec4(src);
+            vv[2 * u + 1] = load_vec4(src + 4);
+            if (tok >= valid) vv[2 * u] = vv[2 * u + 1] = zero4;
+        }
+    };
+    auto stage_v = [&](const f32x4 (&vv)[2 * kPerV], int id) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kPerV; ++u) {
+            const int piece = id + u * kThreads, tok = piece / (DV / 8), c = piece % (DV / 8);
+            const Op3 v3 = op3(vv[2 * u], vv[2 * u + 1]);
+            *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV, tok, c)) = v3.h;
+            *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV + kC * DV, tok, c)) = v3.m;
+            *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV + 2 * kC * DV, tok, c)) = v3.l;
+        }
+    };
+    f32x4 vv[2 * kPerV];
+    load_v(vv, tid);
     // G_c's rows as operand halves, all on their way before the products that come first
     const float* Gc = static_cast<const float*>(a.Gs) + (bh * s.n_chunks + n_chunk) * int64_t(DV) * DK;
     constexpr int kAhead = 4;  // row tiles in flight (64 registers)
-    f32x4 gv[kAhead][KS][2];
-    auto load_g = [&](int mt) __attribute__((always_inline)) {
+    auto load_g = [&](f32x4 (&gv)[2 * KS], int mt) __attribute__((always_inline)) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-                gv[mt % kAhead][ks][hh] = load_vec4(Gc + (16 * mt + n) * DK + 32 * ks + 16 * hh + 4 * g);
+            for (int hh = 0; hh < 2; ++hh) gv[2 * ks + hh] = load_vec4(Gc + (16 * mt + n) * DK + 32 * ks + 16 * hh + 4 * g);
     };
+    auto times_x = [&](const f32x4 (&gv)[2 * KS], const Op3 (&xv)[KS]) __attribute__((always_inline)) -> f32x4 {
+        f32x4 o = zero4;
 #pragma unroll
-    for (int mt = 0; mt < kAhead; ++mt) load_g(mt);
+        for (int ks = 0; ks < KS; ++ks) o = mfma6(op3(gv[2 * ks], gv[2 * ks + 1]), xv[ks], o);
+        return o;
+    };
+    f32x4 gv[kAhead][2 * KS];
+#pragma unroll
+    for (int mt = 0; mt < kAhead; ++mt) load_g(gv[mt], mt);
+    const int reach_x = reach_of(x);
+    const float back = lift_by(2 - reach_x);
+    if (reach_x != 1) scale(x, lift_by(reach_x));
     Op3 xv[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) xv[ks] = op3(x[2 * ks], x[2 * ks + 1]);
@@ -492,23 +554,8 @@ void chunk_cg_f32_split_kernel(CgArgs a)
     Op3 so[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) so[u] = op3(sp[2 * u], sp[2 * u + 1]);
-    __syncthreads();  // every wave is done with its key operands
-#pragma unroll
-    for (int u = 0; u < kPerV; ++u) {
-        const int piece = tid + u * kThreads, tok = piece / (DV / 8), c = piece % (DV / 8);
-        const Op3 v3 = op3(vv[u][0], vv[u][1]);
-        *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV, tok, c)) = v3.h;
-        *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV + kC * DV, tok, c)) = v3.m;
-        *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV + 2 * kC * DV, tok, c)) = v3.l;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int mt = 0; mt < MTV; ++mt) {
-        f32x4 o = zero4;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) o = mfma6(op3(gv[mt % kAhead][ks][0], gv[mt % kAhead][ks][1]), xv[ks], o);
-        if (mt + kAhead < MTV) load_g(mt + kAhead);
-        o *= zeta;
+    // o + the staged values' part of row tile mt
+    auto add_values = [&](f32x4 o, int mt) __attribute__((always_inline)) -> f32x4 {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (2 * u > wave) continue;
@@ -521,6 +568,45 @@ void chunk_cg_f32_split_kernel(CgArgs a)
             };
             o = mfma6(Op3{pair(sV), pair(sV + kC * DV), pair(sV + 2 * kC * DV)}, so[u], o);
         }
+        return o;
+    };
+    __syncthreads();  // every wave is done with its key operands
+    stage_v(vv, tid);
+    __syncthreads();
+    float sum = 0.0f;  // of this lane's |outputs|
+#pragma unroll
+    for (int mt = 0; mt < MTV; ++mt) {
+        f32x4 o = times_x(gv[mt % kAhead], xv);
+        if (mt + kAhead < MTV) load_g(gv[mt % kAhead], mt + kAhead);
+        o = add_values(o * zeta, mt) * back;
+        sum += (fabsf(o[0]) + fabsf(o[1])) + (fabsf(o[2]) + fabsf(o[3]));
+        if (j < valid) *reinterpret_cast<f32x4*>(a.out + (tok0 + j) * DV + 16 * mt + 4 * g) = o;
+    }
+    // A sub-chunk whose outputs are all tiny or not all finite may owe it to values or a state at an
+    // end of fp32: its read-out is done again with those lifted, row tile by row tile.  (Lifting
+    // them in the loop above: B1 H2 T256 34.1 us; this way 32.9.)
+    const bool again = 16 * wave < valid && (!__any(j < valid && sum >= 0x1p-60f) || __any(j < valid && !(sum < INFINITY)));
+    if (lane == 0) sReach[wave] = again;
+    __syncthreads();
+    if (!(sReach[0] | sReach[1] | sReach[2] | sReach[3])) return;
+    int id = tid;
+    asm volatile("" : "+v"(id));  // addresses are formed again, not kept
+    load_v(vv, id);
+    const int rv = reach_of(vv);
+    __syncthreads();  // every wave has read the flags
+    if (lane == 0) sReach[wave] = rv;
+    __syncthreads();
+    const int reach_v = max(max(sReach[0], sReach[1]), max(sReach[2], sReach[3]));
+    scale(vv, lift_by(reach_v));
+    stage_v(vv, id);
+    __syncthreads();
+    if (!again) return;
+#pragma unroll 1
+    for (int mt = 0; mt < MTV; ++mt) {
+        load_g(gv[0], mt);
+        const int reach_g = reach_of(gv[0]);
+        scale(gv[0], lift_by(reach_g));
+        const f32x4 o = times_x(gv[0], xv) * (zeta * lift_by(2 - reach_g) * back) + add_values(zero4, mt) * (lift_by(2 - reach_v) * back);
         if (j < valid) *reinterpret_cast<f32x4*>(a.out + (tok0 + j) * DV + 16 * mt + 4 * g) = o;
     }
 }

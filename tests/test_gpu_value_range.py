@@ -148,3 +148,44 @@ def test_jacobi_start_divides(dk, exponent):
     want = q.double() / 2.0 ** exponent
     torch.cuda.synchronize()
     assert float((got.double() - want).norm() / want.norm()) <= (1e-7 if exponent == 120 else 2.0 ** -18)
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64)])
+@pytest.mark.parametrize("v_exp,a_exp", [(-120, 0), (-112, 0), (-104, 0), (100, 0), (120, 0), (0, 100), (0, 110), (0, 120), (-116, 110)])
+def test_fp32_products_scale_by_powers_of_two(dk, dv, v_exp, a_exp):
+    """fp32 products: values times 2^a scale the outputs by it, and H + Lambda times 2^b (keys times
+    2^(b/2)) by 2^(-b/2), to the rounding that is left where numbers reach below 2^-126 (outputs of
+    2^-120 beside steps of 2^-149 and solutions of 2^-120 alike: 1e-7; ten times that allowed)."""
+    g = torch.Generator(device="cuda").manual_seed(dk + dv)
+    n, t = 3, 150
+    q, k = (torch.randn((1, n, t, dk), generator=g, device="cuda") for _ in range(2))
+    v = torch.randn((1, n, t, dv), generator=g, device="cuda").clamp(-4, 4)
+    q, k = q / q.norm(dim=-1, keepdim=True), k / k.norm(dim=-1, keepdim=True)
+    gamma, beta = torch.sigmoid(torch.randn((1, n, t), generator=g, device="cuda") + 4), torch.rand((1, n, t), generator=g, device="cuda")
+    lam = torch.rand((n, dk), generator=g, device="cuda") + 0.25
+
+    def run(ve, ae):
+        out = L.forward(q, k * 2.0 ** (ae // 2), v * 2.0 ** ve, gamma, beta, lam * 2.0 ** ae, 10, 64, L.MESA_PREC_F32)
+        return out.double() / 2.0 ** (ve - ae // 2)
+
+    want, got = run(0, 0), run(v_exp, a_exp)
+    torch.cuda.synchronize()
+    err = float((got - want).norm() / want.norm())
+    # outputs of 2^(v_exp - a_exp / 2) below 2^-126 are multiples of 2^-149
+    floor = 2.0 ** (-149 - (v_exp - a_exp // 2)) if v_exp - a_exp // 2 < -120 else 0.0
+    assert err <= 1e-6 + 4 * floor, err
+
+
+@pytest.mark.parametrize("dk", [64, 128])
+def test_fp32_products_of_the_largest_values(dk):
+    """One token with values up to the largest finite number: o = beta v (k . q*), finite, to fp32 rounding."""
+    dv = 64
+    g = torch.Generator(device="cuda").manual_seed(dk)
+    q, k = (torch.randn((1, 1, 1, dk), generator=g, device="cuda") for _ in range(2))
+    q, k = q / q.norm(), k / k.norm()
+    v = torch.linspace(-1, 1, dv, device="cuda", dtype=torch.float64).mul(3.4028234e38).float().reshape(1, 1, 1, dv)
+    beta = torch.full((1, 1, 1), 0.5, device="cuda")
+    res = L.forward(q, k, v, torch.ones_like(beta), beta, torch.ones((1, dk), device="cuda"), 4, 64, L.MESA_PREC_F32, want_qstar=True)
+    torch.cuda.synchronize()
+    want = 0.5 * v.double() * (k.double() * res["qstar"].double()).sum()
+    assert float((res["out"].double() - want).norm() / want.norm()) <= 1e-6 / abs(float((k.double() * res["qstar"].double()).sum()))
