@@ -162,14 +162,7 @@ __device__ __forceinline__ f32x4 load_vec4(const bf16_t* p)
                  __uint_as_float(u.y & 0xffff0000u)};
 }
 
-// A token-major tile of 64 rows of D bf16 in LDS: 16-byte piece c of token i sits at piece
-// c ^ (i mod 8) of its row, which spreads row reads (16 tokens, one feature group) and the
-// transposing reads over the banks.
-template <int D>
-__device__ __forceinline__ uint16_t* tile_piece(uint16_t* tile, int tok, int c)
-{
-    return tile + tok * D + 8 * (c ^ (tok % 8));
-}
+constexpr int kSwizzle = 8;  // of the token-major tiles: also spreads reads of one feature group of 16 tokens
 
 // Operand with rows = tokens 16 i + n, contraction = features 32 s ..: two 8-byte reads at a
 // lane offset that is formed once (bytes; the piece index is its bits above 16 bytes, rows
@@ -184,21 +177,6 @@ __device__ __forceinline__ bf16x8 row_frag_at(const uint16_t* tile, uint32_t off
     const char* base = reinterpret_cast<const char*>(tile);
     return halves(*reinterpret_cast<const uint2*>(base + (off ^ (4 * s * 16))),
                   *reinterpret_cast<const uint2*>(base + (off ^ ((4 * s + 2) * 16))));
-}
-
-// Half an operand with rows = features 16 t + n, contraction = tokens 16 i ..: a transposing
-// read (of each 16 lanes, lane l points at four features of row l / 4; lane n receives feature
-// n of the four rows).
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-template <int D>
-__device__ __forceinline__ uint2 tile_col_half(uint16_t* tile, int t, int i, int g, int n)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    uint16_t* src = tile_piece<D>(tile, 16 * i + 4 * g + n / 4, 2 * t + n % 4 / 2) + 4 * (n % 2);
-    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src)));
-#else
-    return uint2{};
-#endif
 }
 
 // beta_i prod_{s=i+1..j} gamma_s for the tokens i = i4 .. i4+3 (zero for i > j): lgj = lg[j], zlj = zl[j].
@@ -290,9 +268,9 @@ void chunk_cg_f32_split_kernel(CgArgs a)
         const int piece = tid + u * kThreads, tok = piece / (DK / 8), c = piece % (DK / 8);
         if (tok >= valid) kv[u][0] = kv[u][1] = zero4;
         const Op3 k3 = op3(kv[u][0], kv[u][1]);
-        *reinterpret_cast<bf16x8*>(tile_piece<DK>(sK[0], tok, c)) = k3.h;
-        *reinterpret_cast<bf16x8*>(tile_piece<DK>(sK[1], tok, c)) = k3.m;
-        *reinterpret_cast<bf16x8*>(tile_piece<DK>(sK[2], tok, c)) = k3.l;
+        *reinterpret_cast<bf16x8*>(tile_piece<DK, kSwizzle>(sK[0], tok, c)) = k3.h;
+        *reinterpret_cast<bf16x8*>(tile_piece<DK, kSwizzle>(sK[1], tok, c)) = k3.m;
+        *reinterpret_cast<bf16x8*>(tile_piece<DK, kSwizzle>(sK[2], tok, c)) = k3.l;
     }
     __syncthreads();
 
@@ -307,8 +285,8 @@ void chunk_cg_f32_split_kernel(CgArgs a)
     Half3 kh[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t)
-        kh[t] = Half3{tile_col_half<DK>(sK[0], t, wave, g, n), tile_col_half<DK>(sK[1], t, wave, g, n),
-                      tile_col_half<DK>(sK[2], t, wave, g, n)};
+        kh[t] = Half3{tile_col_half<DK, kSwizzle>(sK[0], t, wave, g, n), tile_col_half<DK, kSwizzle>(sK[1], t, wave, g, n),
+                      tile_col_half<DK, kSwizzle>(sK[2], t, wave, g, n)};
 
     // ---- E_w (the last wave's is not needed), then B_w, and its parts as operands.  Tile
     // (rt, ct) of E holds rows 16 rt + 4 g .., column 16 ct + n: the layout of hacc[ct][rt / 2][rt % 2].
@@ -501,9 +479,9 @@ void chunk_cg_f32_split_kernel(CgArgs a)
         for (int u = 0; u < kPerV; ++u) {
             const int piece = id + u * kThreads, tok = piece / (DV / 8), c = piece % (DV / 8);
             const Op3 v3 = op3(vv[2 * u], vv[2 * u + 1]);
-            *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV, tok, c)) = v3.h;
-            *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV + kC * DV, tok, c)) = v3.m;
-            *reinterpret_cast<bf16x8*>(tile_piece<DV>(sV + 2 * kC * DV, tok, c)) = v3.l;
+            *reinterpret_cast<bf16x8*>(tile_piece<DV, kSwizzle>(sV, tok, c)) = v3.h;
+            *reinterpret_cast<bf16x8*>(tile_piece<DV, kSwizzle>(sV + kC * DV, tok, c)) = v3.m;
+            *reinterpret_cast<bf16x8*>(tile_piece<DV, kSwizzle>(sV + 2 * kC * DV, tok, c)) = v3.l;
         }
     };
     f32x4 vv[2 * kPerV];
@@ -563,8 +541,8 @@ void chunk_cg_f32_split_kernel(CgArgs a)
             // NaN among them must not reach this sub-chunk's tokens
             const uint32_t keep = 2 * u + 1 <= wave ? ~0u : 0u;
             auto pair = [&](uint16_t* tv) __attribute__((always_inline)) -> bf16x8 {
-                const uint2 later = tile_col_half<DV>(tv, mt, 2 * u + 1, g, n);
-                return halves(tile_col_half<DV>(tv, mt, 2 * u, g, n), make_uint2(later.x & keep, later.y & keep));
+                const uint2 later = tile_col_half<DV, kSwizzle>(tv, mt, 2 * u + 1, g, n);
+                return halves(tile_col_half<DV, kSwizzle>(tv, mt, 2 * u, g, n), make_uint2(later.x & keep, later.y & keep));
             };
             o = mfma6(Op3{pair(sV), pair(sV + kC * DV), pair(sV + 2 * kC * DV)}, so[u], o);
         }

@@ -412,34 +412,12 @@ __global__ __launch_bounds__(kThreads) void chunk_state_f32_kernel(StateArgs a)
     }
 }
 
-// A token-major tile of 64 rows of D bf16 in LDS: 16-byte piece c of token i sits at piece
-// c ^ (i mod D / 8) of its row, which spreads the rows' writes and the transposing reads below
-// evenly over the banks.
-template <int D>
-__device__ __forceinline__ uint16_t* tile_piece(uint16_t* tile, int tok, int c)
-{
-    return tile + tok * D + 8 * (c ^ (tok % (D / 8)));
-}
-
-// Operand fragment with rows (or columns) = features 16 t + n, contraction = tokens 32 u ..:
-// two transposing reads (of each 16 lanes, lane l points at four features of row l / 4; lane n
-// receives feature n of the four rows).
-typedef short s16x4 __attribute__((ext_vector_type(4)));
+// Operand with rows (or columns) = features 16 t + n, contraction = tokens 32 u ..
 template <int D>
 __device__ __forceinline__ bf16x8 tile_col_frag(uint16_t* tile, int t, int u, int g, int n)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
-    uint2 r[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int tl = 4 * g + n / 4;  // token within its 16
-        uint16_t* src = tile + (32 * u + 16 * h) * D + tl * D + 8 * ((2 * t + n % 4 / 2) ^ (tl % (D / 8))) + 4 * (n % 2);
-        r[h] = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src)));
-    }
-    return __builtin_bit_cast(bf16x8, make_uint4(r[0].x, r[0].y, r[1].x, r[1].y));
-#else
-    return bf16x8{};
-#endif
+    const uint2 lo = tile_col_half<D, D / 8>(tile, t, 2 * u, g, n), hi = tile_col_half<D, D / 8>(tile, t, 2 * u + 1, g, n);
+    return __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
 }
 
 // Wide variant (bf16 k and v, chunk 64, d_k and d_v in {64, 128}), used for the
@@ -610,9 +588,9 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             for (int m = 0; m < (WK ? NY : NK); ++m) {
                 const int i = tid + m * kWideThreads;
                 if constexpr (WK)
-                    *reinterpret_cast<uint4*>(tile_piece<NC>(sB[b][0], i / PY, i % PY)) = y_piece(R, m);
+                    *reinterpret_cast<uint4*>(tile_piece<NC, NC / 8>(sB[b][0], i / PY, i % PY)) = y_piece(R, m);
                 else
-                    *reinterpret_cast<uint4*>(tile_piece<DK>(sA[b][0], i / PK, i % PK)) = R.k[m];
+                    *reinterpret_cast<uint4*>(tile_piece<DK, DK / 8>(sA[b][0], i / PK, i % PK)) = R.k[m];
             }
         };
         auto stage_weighted = [&](const Regs& R, int b, const Gate& gt, int m) {
@@ -632,8 +610,8 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
             }
             auto put = [&](int plane, const uint32_t (&u)[4]) {
                 uint16_t* dst;
-                if constexpr (WK) dst = tile_piece<DK>(sA[b][plane], i / PK, i % PK);
-                else dst = tile_piece<NC>(sB[b][plane], i / PY, i % PY);
+                if constexpr (WK) dst = tile_piece<DK, DK / 8>(sA[b][plane], i / PK, i % PK);
+                else dst = tile_piece<NC, NC / 8>(sB[b][plane], i / PY, i % PY);
                 *reinterpret_cast<uint4*>(dst) = make_uint4(u[0], u[1], u[2], u[3]);
             };
             put(0, hi);
@@ -682,17 +660,14 @@ __global__ __launch_bounds__(kWideThreads) void chunk_state_wide_kernel(StateArg
                 const int64_t lo_plane = s.batch * s.heads * int64_t(s.n_chunks) * kStateElems;
 #pragma unroll
                 for (int ct = 0; ct < NCT; ++ct) {
-                    const uint4 pk = make_uint4(pack_bf16x2(acc[0][ct][0], acc[0][ct][1]), pack_bf16x2(acc[0][ct][2], acc[0][ct][3]),
-                                                pack_bf16x2(acc[1][ct][0], acc[1][ct][1]), pack_bf16x2(acc[1][ct][2], acc[1][ct][3]));
                     const int64_t off = (((ct0 + ct) * NS + sblk) * kWave + lane) * 8;
-                    *reinterpret_cast<uint4*>(base + off) = pk;
                     if constexpr (X3) {
-                        auto lo2 = [](float x0, float x1, uint32_t h) {
-                            return pack_bf16x2(x0 - __uint_as_float(h << 16), x1 - __uint_as_float(h & 0xffff0000u));
-                        };
-                        const uint4 pl = make_uint4(lo2(acc[0][ct][0], acc[0][ct][1], pk.x), lo2(acc[0][ct][2], acc[0][ct][3], pk.y),
-                                                    lo2(acc[1][ct][0], acc[1][ct][1], pk.z), lo2(acc[1][ct][2], acc[1][ct][3], pk.w));
-                        *reinterpret_cast<uint4*>(base + lo_plane + off) = pl;
+                        bf16x8 hi, lo;
+                        split8(acc[0][ct], acc[1][ct], hi, lo);
+                        *reinterpret_cast<bf16x8*>(base + off) = hi;
+                        *reinterpret_cast<bf16x8*>(base + lo_plane + off) = lo;
+                    } else {
+                        *reinterpret_cast<bf16x8*>(base + off) = pack8(acc[0][ct], acc[1][ct]);
                     }
                 }
             }

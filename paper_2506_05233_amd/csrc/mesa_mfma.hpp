@@ -88,6 +88,31 @@ __device__ __forceinline__ bf16x8 lds_frag(const uint16_t* base)
     return __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
 }
 
+// A token-major tile of rows of D bf16 in LDS: 16-byte piece c of token i sits at piece
+// c ^ (i mod SW) of its row (SW 8 or 16, at most the D / 8 pieces of a row), which spreads the
+// rows' writes and the transposing reads below evenly over the banks.
+template <int D, int SW>
+__device__ __forceinline__ uint16_t* tile_piece(uint16_t* tile, int tok, int c)
+{
+    static_assert(SW <= D / 8 && 16 % SW == 0, "pieces stay in their row, in the same place every 16 tokens");
+    return tile + tok * D + 8 * (c ^ (tok % SW));
+}
+
+// Half an operand with rows (or columns) = features 16 t + n, contraction = tokens 16 i ..: a
+// transposing read (of each 16 lanes, lane l points at four features of row l / 4; lane n receives
+// feature n of the four rows).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+template <int D, int SW>
+__device__ __forceinline__ uint2 tile_col_half(uint16_t* tile, int t, int i, int g, int n)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint16_t* src = tile_piece<D, SW>(tile + 16 * i * D, 4 * g + n / 4, 2 * t + n % 4 / 2) + 4 * (n % 2);
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src)));
+#else
+    return uint2{};
+#endif
+}
+
 // 16 bytes into an LDS row that is only 8-byte aligned, as two 8-byte stores.
 __device__ __forceinline__ void put8x2(uint16_t* dst, const uint4& x)
 {
