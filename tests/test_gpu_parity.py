@@ -804,6 +804,21 @@ def test_chunk_states_from_totals_and_scan(bh, T, dtype, prec, dk, dv):
     assert rel_l2(got, ref) <= tol
 
 
+@pytest.mark.parametrize("dtype,prec", [("f32", L.MESA_PREC_F32), ("bf16", L.MESA_PREC_BF16)])
+@pytest.mark.parametrize("T", [1024 * 64, 1024 * 64 + 1])
+def test_chunk_states_at_the_longest_scan(T, dtype, prec):
+    """One sequence of 1024 chunks, the longest that totals and scan take (fp32), and of 1025, which
+    walk: the last 2048 outputs, which every chunk before reaches through gates near one, against
+    the oracle."""
+    x = W.forward_inputs(1, 1, T, 64, 64, dtype, 5.0, seed=T)
+    x["gamma"][...] = np.maximum(x["gamma"], 0.99995).astype(np.float32)
+    x["beta"] *= np.float32(0.01)  # states of some hundred keys' weight
+    got = _gpu_forward(x, dtype, 4, 64, precision=prec)
+    ref = oracle.forward(x["q"], x["k"], x["v"], x["gamma"], x["beta"], x["lam"], 4)["out"]
+    tail = slice(T - 2048, T)
+    assert rel_l2(got[:, :, tail], ref[:, :, tail]) <= (TOL_BF16 if prec == L.MESA_PREC_BF16 else 1e-5)
+
+
 @pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
 def test_packed_states_streamed_match_kept(dk, dv):
     """Packed states just above 384 MB take the streaming kernel, the two halves of the same pairs

@@ -76,8 +76,9 @@ def reports():
 
 def test_every_source_reports_its_kernels(reports):
     kinds = ["chunk_cg_bf16_kernel", "chunk_cg_x3_kernel", "chunk_cg_f32_mma_kernel", "chunk_cg_f32_split_kernel", "chunk_state_wide_kernel",
-             "decode_step_kernel", "bwd_grad_kernel", "bwd_adjoint_kernel", "bwd_rhs_kernel", "frontend_kernel",
-             "output_norm_kernel"]
+             "chunk_state_f32_kernel", "segment_combine_kernel", "chunk_scan_kernel", "decode_step_kernel", "decode_stream_kernel",
+             "decode_few_kernel", "bwd_grad_kernel", "bwd_adjoint_kernel", "bwd_adjoint_scan_kernel", "bwd_dlam_kernel",
+             "bwd_rhs_kernel", "frontend_kernel", "output_norm_kernel"]
     for k in kinds:
         assert any(k in name for name in reports), k
 
