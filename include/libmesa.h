@@ -154,9 +154,9 @@ int mesa_forward(const void* q, const void* k, const void* v, const float* gamma
  * qstar_out must be NULL, final_H and final_G must be given, and workspace may
  * be NULL with workspace_bytes 0.  A workspace given to such a call must hold
  * mesa_forward_workspace_bytes(...) (MESA_ERR_WORKSPACE otherwise) and overlap
- * no input or output (MESA_ERR_ARG); the scan then uses it as scratch, which
+ * no input or output (MESA_ERR_ARG); the scan then uses all of it as scratch, which
  * lets it split the walk over the chunks into segments that run side by side
- * when there are few sequences (see mesa_forward_states). */
+ * where that is faster (see mesa_forward_states). */
 int mesa_forward_ex(const void* q, const void* k, const void* v, const float* gamma,
                     const float* beta, const float* lambda, int64_t batch, int64_t heads,
                     int64_t seq_len, int64_t d_k, int64_t d_v, int dtype, int n_cg, int chunk,
@@ -209,7 +209,11 @@ int mesa_forward_solve(const void* q, const void* k, const void* v, const float*
  *   gamma, beta [batch, heads]        fp32
  *   lambda  [heads, d_k]              fp32
  *   out     [batch, heads, d_v]       fp32
- * Arithmetic is fp32 throughout. */
+ * Arithmetic is fp32 throughout.  H is symmetric, and either of H[i][j] and H[j][i]
+ * may be read for the product.  The number of pairs and the alignment of the states
+ * choose the kernel (up to 65536 / d_k pairs, on states aligned to 16 bytes, take one
+ * built for latency): the new states of a pair are the same bits in every kernel, its
+ * output, and under a tolerance its iteration count, the same up to fp32 rounding. */
 int mesa_decode_step(float* state_H, float* state_G, const void* q, const void* k, const void* v,
                      const float* gamma, const float* beta, const float* lambda, int64_t batch,
                      int64_t heads, int64_t d_k, int64_t d_v, int dtype, int n_cg, float* out,

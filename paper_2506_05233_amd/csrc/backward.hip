@@ -1487,7 +1487,8 @@ hipError_t launch_bwd_dims(const BwdArgs& a, hipStream_t stream, int stage)
             // the rounds of the totals, but move the adjoints twice more (~2.7 MB per us) and
             // cost a launch.  One step of walk saved is worth 12 MB, the launch 11 MB (backward,
             // walk / scan: 8 sequences of 13 chunks d 64 fp32 128 / 86 us, 16 of 64 d 128 bf16
-            // 558 / 495, 16 of 256 2124 / 1812; not 64 of 16: 464 / 480, 128 of 5: 282 / 305).
+            // 558 / 495, 16 of 256 2124 / 1812; not 64 of 16: 464 / 480, 128 of 5: 282 / 305; over
+            // 606 shapes to 400 MB of adjoints the backward is within 4% of the faster form).
             const int64_t bytes = bh * nc * int64_t(DK) * (DK + DV) * 4;
             const int64_t resident = 512;  // workgroups the chip holds at once
             const int64_t walk = (S > 1 ? 2 * len : nc) * ((bh * NTILE * S + resident - 1) / resident);

@@ -461,7 +461,7 @@ __device__ __forceinline__ bf16x8 tile_col_frag(uint16_t* tile, int t, int u, in
 // applied to whole segments -- and walks the segment's chunks as above.  A states-only call
 // needs no second walk: all its segments run side by side in the first launch and a small
 // kernel combines their totals (4 x 16 sequences of 4001 tokens, d 128: 140 us with the last
-// segment walked after the others, 62 us combined).
+// segment walked after the others, 62 us combined).  The plans are chosen in scan_plan.hpp.
 constexpr int kWideThreads = 512;  // eight waves: two per SIMD
 
 // Segments of one launch of the wide scan.
