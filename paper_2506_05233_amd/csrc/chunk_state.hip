@@ -982,7 +982,8 @@ __global__ __launch_bounds__(kThreads) void chunk_scan_kernel(StateArgs a, int64
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int64_t tok = int64_t(n0 + 4 * wave + u) * 64 + lane;
-            gm[u] = tok < s.seq_len ? a.gamma[bh * s.seq_len + tok] : 1.0f;
+            const float gt = tok < s.seq_len ? a.gamma[bh * s.seq_len + tok] : 1.0f;
+            gm[u] = gt > 0.0f ? gt : 0.0f;  // a gate that is not positive resets, as in the walks
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {

@@ -189,3 +189,30 @@ def test_fp32_products_of_the_largest_values(dk):
     torch.cuda.synchronize()
     want = 0.5 * v.double() * (k.double() * res["qstar"].double()).sum()
     assert float((res["out"].double() - want).norm() / want.norm()) <= 1e-6 / abs(float((k.double() * res["qstar"].double()).sum()))
+
+
+@pytest.mark.parametrize("dtype,prec", [(torch.float32, L.MESA_PREC_F32), (torch.bfloat16, L.MESA_PREC_BF16X3),
+                                        (torch.bfloat16, L.MESA_PREC_BF16)])
+@pytest.mark.parametrize("t", [32 * 64, 3 * 64])
+@pytest.mark.parametrize("gate", [-0.5, float("nan")])
+def test_gates_that_are_not_positive_reset(gate, t, dtype, prec):
+    """A gate that is negative or NaN resets the states like a zero gate, bit for bit, in the forward
+    and its gradients, whichever form the state pass takes (chunk totals and a scan, or a walk)."""
+    g = torch.Generator(device="cuda").manual_seed(t)
+    n, d = 2, 64
+    q, k, v = (torch.randn((1, n, t, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    gamma = 1.0 - 0.01 * torch.rand((1, n, t), generator=g, device="cuda")
+    beta = torch.rand((1, n, t), generator=g, device="cuda")
+    lam = torch.rand((n, d), generator=g, device="cuda") + 0.25
+    dout = torch.randn((1, n, t, d), generator=g, device="cuda")
+
+    def run(value):
+        gm = gamma.clone()
+        gm[0, 0, t // 3] = value
+        f = L.forward(q, k, v, gm, beta, lam, 6, 64, prec, want_qstar=True)
+        b = L.backward(k, v, gm, beta, lam, f["qstar"], dout, 6)
+        torch.cuda.synchronize()
+        return [f["out"], f["qstar"]] + [b[x] for x in ("dq", "dk", "dv", "dgamma", "dbeta", "dlam")]
+
+    for a, b in zip(run(0.0), run(gate)):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
