@@ -129,7 +129,8 @@ __device__ __forceinline__ f32x4 join3(const Half3& a)
 
 // Operands that lie at an end of fp32 are brought into the range that splits exactly by a power of
 // two, which the result gives back: reach 0 stands for numbers all below 2^-60, 2 for some from
-// 2^127 on, 1 for others (the same for every lane of a wave).
+// 2^127 on, 1 for others (the same for every lane of a wave).  The keys are split as they are (the
+// parts of one of 2^-110 still hold 23 bits of it; its square is long gone from H).
 __device__ __forceinline__ float lift_by(int reach) { return reach == 0 ? 0x1p60f : reach == 2 ? 0x1p-60f : 1.0f; }
 __device__ __forceinline__ int reach_of(float largest)
 {
@@ -280,7 +281,6 @@ void chunk_cg_f32_split_kernel(CgArgs a)
     const int jb = 16 * wave - 1, je = 16 * wave + 15;  // the sub-chunk's entering and last token
     // decay from the sub-chunk's entering state to token j
     const float zs = wave == 0 ? decay_from_start(sLg, sZl, j) : decay_between(sLg, sZl, jb, j);
-    const float zeta = decay_from_start(sLg, sZl, j);
     const f32x4 zw = decay_weights4(sLg, sBeta, lgj, zlj, 16 * wave + 4 * g, j);
     Half3 kh[MT];
 #pragma unroll
@@ -306,6 +306,7 @@ void chunk_cg_f32_split_kernel(CgArgs a)
 #pragma unroll
     for (int v = 0; v < kWaves - 1; ++v) zv[v] = v < wave ? decay_between(sLg, sZl, 16 * v + 15, jb) : 0.0f;
     Op3 hf[MT][KS];
+    float zh;  // zs, and what takes the lift of hf back
     {
         const float z0 = wave == 0 ? 1.0f : decay_from_start(sLg, sZl, jb);
 #pragma unroll
@@ -325,17 +326,31 @@ void chunk_cg_f32_split_kernel(CgArgs a)
                         for (int hh = 0; hh < 2; ++hh)
                             hacc[mt][ks][hh] += zv[v] * sE[((v * MT + mt) * MT + 2 * ks + hh) * kWave + lane];
             }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) hf[mt][ks] = op3(hacc[mt][ks][0], hacc[mt][ks][1]);
-        // diagonal: row 16 mt + n of row tile mt sits at 4 g + e = n
+        // diagonal: row 16 mt + n of row tile mt sits at 4 g + e = n.  B_w is positive semidefinite, so no
+        // element is larger than the largest of it.
+        float top = 0.0f;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const f32x4 d = hacc[mt][mt / 2][mt % 2];
             const int e = n - 4 * g;
-            if (e >= 0 && e < 4) sDiag[wave][16 * mt + n] = e == 0 ? d[0] : e == 1 ? d[1] : e == 2 ? d[2] : d[3];
+            if (e >= 0 && e < 4) {
+                const float de = e == 0 ? d[0] : e == 1 ? d[1] : e == 2 ? d[2] : d[3];
+                sDiag[wave][16 * mt + n] = de;
+                top = fmaxf(top, de);
+            }
         }
+        const int reach_h = reach_of(top);
+        zh = zs * lift_by(2 - reach_h);
+        if (reach_h != 1) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) scale(hacc[mt][ks], lift_by(reach_h));
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) hf[mt][ks] = op3(hacc[mt][ks][0], hacc[mt][ks][1]);
     }
 
     __syncthreads();  // every wave is done with the sums
@@ -380,7 +395,7 @@ void chunk_cg_f32_split_kernel(CgArgs a)
         for (int mt = 0; mt < MT; ++mt) {
             const f32x4 lam = *reinterpret_cast<const f32x4*>(sLam + 16 * mt + 4 * g);
             const Left16 kl = Left16{sKL[klo + 3 * mt * kWave], sKL[klo + (3 * mt + 1) * kWave], sKL[klo + (3 * mt + 2) * kWave]};
-            w[mt] = mfma6(kl, sb, zs * w[mt] + lam * vec[mt]);
+            w[mt] = mfma6(kl, sb, zh * w[mt] + lam * vec[mt]);
         }
     };
 
@@ -392,22 +407,27 @@ void chunk_cg_f32_split_kernel(CgArgs a)
         const float qs = __builtin_ldexpf(1.0f, -qsh);
         const Right16 zb = right16(split3(zw));
         f32x4 d[MT];
-        float least = INFINITY;
+        float least = INFINITY, top = 0.0f;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) top = largest4(top, join3(kh[t]));
+        // squares of keys below 2^-30 or from 2^63 on lie at an end of fp32
+        const float kup = !__any(top >= 0x1p-30f) ? 0x1p30f : __any(top >= 0x1p63f) ? 0x1p-30f : 1.0f, kback = 1.0f / (kup * kup);
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
-            const f32x4 k = join3(kh[t]);
+            const f32x4 k = kup * join3(kh[t]);
             const f32x4 acc = mfma6(left16(split3(k * k)), zb, zero4);
             qv[t] *= qs;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int f = 16 * t + 4 * g + e;
-                d[t][e] = zs * sDiag[wave][f] + acc[e] + sLam[f];
+                d[t][e] = zs * sDiag[wave][f] + kback * acc[e] + sLam[f];
                 least = fminf(least, d[t][e]);
             }
         }
-        // a large system has a small x; CG's other directions are residuals of a unit q
-        const bool large = !__any(least < 0x1p60f);
-        const float up = large ? 0x1p60f : 1.0f, down = large ? 0x1p-60f : 1.0f;
+        // a large system has a small x, a tiny one a large x; CG's other directions are residuals
+        // of a unit q
+        const bool large = !__any(least < 0x1p60f), tiny = __any(least < 0x1p-100f);
+        const float up = large ? 0x1p60f : tiny ? 0x1p-60f : 1.0f, down = large ? 0x1p-60f : tiny ? 0x1p60f : 1.0f;
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
 #pragma unroll
@@ -510,6 +530,9 @@ void chunk_cg_f32_split_kernel(CgArgs a)
     Op3 xv[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) xv[ks] = op3(x[2 * ks], x[2 * ks + 1]);
+    int jr = j, nr = n;
+    asm volatile("" : "+v"(jr), "+v"(nr));  // decays and addresses are formed again, not kept through CG
+    const float zeta = decay_from_start(sLg, sZl, jr), zr = wave == 0 ? zeta : decay_between(sLg, sZl, jb, jr);
     // S' over the token tiles, as right operands of two 32-token steps.  Every wave forms all
     // four tiles (the last wave needs them, and the others wait for it) and drops the ones past
     // its own; the weight of an earlier sub-chunk's token is the product of three decays.
@@ -525,7 +548,7 @@ void chunk_cg_f32_split_kernel(CgArgs a)
     }
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
-        const f32x4 wt = it == wave ? zw : zs * (zv[it < kWaves - 1 ? it : 0] * *reinterpret_cast<const f32x4*>(sWe + 16 * it + 4 * g));
+        const f32x4 wt = it == wave ? zw : zr * (zv[it < kWaves - 1 ? it : 0] * *reinterpret_cast<const f32x4*>(sWe + 16 * it + 4 * g));
 #pragma unroll
         for (int e = 0; e < 4; ++e) sp[it][e] = 16 * it + 4 * g + e <= j ? sp[it][e] * wt[e] : 0.0f;
     }
@@ -541,8 +564,8 @@ void chunk_cg_f32_split_kernel(CgArgs a)
             // NaN among them must not reach this sub-chunk's tokens
             const uint32_t keep = 2 * u + 1 <= wave ? ~0u : 0u;
             auto pair = [&](uint16_t* tv) __attribute__((always_inline)) -> bf16x8 {
-                const uint2 later = tile_col_half<DV, kSwizzle>(tv, mt, 2 * u + 1, g, n);
-                return halves(tile_col_half<DV, kSwizzle>(tv, mt, 2 * u, g, n), make_uint2(later.x & keep, later.y & keep));
+                const uint2 later = tile_col_half<DV, kSwizzle>(tv, mt, 2 * u + 1, g, nr);
+                return halves(tile_col_half<DV, kSwizzle>(tv, mt, 2 * u, g, nr), make_uint2(later.x & keep, later.y & keep));
             };
             o = mfma6(Op3{pair(sV), pair(sV + kC * DV), pair(sV + 2 * kC * DV)}, so[u], o);
         }

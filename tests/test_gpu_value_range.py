@@ -176,6 +176,27 @@ def test_fp32_products_scale_by_powers_of_two(dk, dv, v_exp, a_exp):
     assert err <= 1e-6 + 4 * floor, err
 
 
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64)])
+@pytest.mark.parametrize("n_cg", [0, 1])
+def test_fp32_products_of_a_tiny_system(dk, dv, n_cg):
+    """fp32 products: H + Lambda times 2^-116 (keys times 2^-58) scales the outputs by 2^58, elements of H
+    of 2^-124 beside steps of 2^-149.  One iteration at most, whose p^T A p is normal (the queries are
+    the keys, weighed by at least a half, so that r_0 is nowhere small): Alg. 1 stops below."""
+    g = torch.Generator(device="cuda").manual_seed(dk + dv)
+    n, t = 3, 150
+    k = torch.randn((1, n, t, dk), generator=g, device="cuda")
+    v = torch.randn((1, n, t, dv), generator=g, device="cuda")
+    k = k / k.norm(dim=-1, keepdim=True)
+    gamma = torch.sigmoid(torch.randn((1, n, t), generator=g, device="cuda") + 4)
+    beta = 0.5 + 0.5 * torch.rand((1, n, t), generator=g, device="cuda")
+    lam = torch.rand((n, dk), generator=g, device="cuda") + 0.25
+    want = L.forward(k, k, v, gamma, beta, lam, n_cg, 64, L.MESA_PREC_F32).double()
+    got = L.forward(k, k * 2.0 ** -58, v, gamma, beta, lam * 2.0 ** -116, n_cg, 64, L.MESA_PREC_F32).double() * 2.0 ** -58
+    torch.cuda.synchronize()
+    err = float((got - want).norm() / want.norm())
+    assert err <= 1e-6, err
+
+
 @pytest.mark.parametrize("dk", [64, 128])
 def test_fp32_products_of_the_largest_values(dk):
     """One token with values up to the largest finite number: o = beta v (k . q*), finite, to fp32 rounding."""
