@@ -25,6 +25,7 @@
 // a = t / C + (256 / C) m, so the per-column CG scalars reduce over 256 / C threads.
 #include "mesa_device.hpp"
 #include "mesa_kernels.hpp"
+#include "mesa_mfma.hpp"
 
 namespace mesa {
 namespace {
@@ -258,23 +259,12 @@ __global__ __launch_bounds__(kThreads) void chunk_cg_f32_kernel(CgArgs a)
 // k-slot g stands for feature 16u + 4g + jj (jj = 0..3), which is where lane (g, l)
 // already holds it; the A operand (H_c, K or K^T from LDS) is read with the same
 // feature order as one 16-byte access.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-
-template <int DK>
-__device__ __forceinline__ f32x4 load_vec4(const float* p) { const float4 v = load4(p); return f32x4{v.x, v.y, v.z, v.w}; }
-template <int DK>
-__device__ __forceinline__ f32x4 load_vec4(const bf16_t* p)
-{
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
-    return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
-                 __uint_as_float(u.y & 0xffff0000u)};
-}
 
 template <typename Tin, int DK, int DV>
 __global__ __launch_bounds__(kThreads) void chunk_cg_f32_mma_kernel(CgArgs a)
@@ -319,7 +309,7 @@ __global__ __launch_bounds__(kThreads) void chunk_cg_f32_mma_kernel(CgArgs a)
 #pragma unroll
         for (int m = 0; m < NKV; ++m) {
             const int f = 4 * (w + (kThreads / kWave) * m);
-            kv[m] = load_vec4<DK>(kp + (tok0 + min(lane, valid - 1)) * DK + f);
+            kv[m] = load_vec4(kp + (tok0 + min(lane, valid - 1)) * DK + f);
         }
 #pragma unroll
         for (int m = 0; m < NV; ++m) {
@@ -343,7 +333,7 @@ __global__ __launch_bounds__(kThreads) void chunk_cg_f32_mma_kernel(CgArgs a)
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         const int64_t off = (tok0 + min(j, valid - 1)) * DK + 16 * t + 4 * g;
-        f32x4 v = a.rhs ? load_vec4<DK>(a.rhs + off) : load_vec4<DK>(static_cast<const Tin*>(a.q) + off);
+        f32x4 v = a.rhs ? load_vec4(a.rhs + off) : load_vec4(static_cast<const Tin*>(a.q) + off);
         qv[t] = j < valid ? v : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
     __syncthreads();
@@ -511,7 +501,7 @@ __global__ __launch_bounds__(kThreads) void chunk_cg_f32_mma_kernel(CgArgs a)
         f32x4 vv[NVV];
 #pragma unroll
         for (int m = 0; m < NVV; ++m)
-            vv[m] = load_vec4<DV>(vp + (tok0 + min(lane, valid - 1)) * DV + 4 * (w + (kThreads / kWave) * m));
+            vv[m] = load_vec4(vp + (tok0 + min(lane, valid - 1)) * DV + 4 * (w + (kThreads / kWave) * m));
 #pragma unroll
         for (int m = 0; m < NG; ++m) {
             const int e = 4 * (tid + kThreads * m);

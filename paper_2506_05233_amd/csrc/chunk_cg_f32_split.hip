@@ -155,14 +155,6 @@ __device__ __forceinline__ void scale(f32x4 (&v)[N], float by)
     for (int i = 0; i < N; ++i) v[i] *= by;
 }
 
-__device__ __forceinline__ f32x4 load_vec4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
-__device__ __forceinline__ f32x4 load_vec4(const bf16_t* p)
-{
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
-    return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
-                 __uint_as_float(u.y & 0xffff0000u)};
-}
-
 constexpr int kSwizzle = 8;  // of the token-major tiles: also spreads reads of one feature group of 16 tokens
 
 // Operand with rows = tokens 16 i + n, contraction = features 32 s ..: two 8-byte reads at a

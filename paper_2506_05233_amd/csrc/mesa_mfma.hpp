@@ -13,10 +13,21 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mesa_device.hpp"
+
 namespace mesa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Four consecutive values, widened to fp32.
+__device__ __forceinline__ f32x4 load_vec4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 load_vec4(const bf16_t* p)
+{
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                 __uint_as_float(u.y & 0xffff0000u)};
+}
 
 __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c)
 {
