@@ -1426,39 +1426,57 @@ __global__ __launch_bounds__(kThreads) void bwd_adjoint_scan_kernel(BwdArgs a, c
 
 // ---------------------------------------------------------------- dLambda
 // dLambda[h][b] = sum over the batch and the chunks of the per-chunk partial sums:
-// one workgroup per head and sixteen features (64 bytes of a row); thread (slot, b) sums
-// every kLamSlots-th (batch, chunk) entry, eight loads in flight at a time into eight
-// partial sums, then the partial sums and the slots are combined in a fixed order.  Bound by
-// the round trips of its loads: B8 H16 T2048 d128 5.7 us, one workgroup per head of four waves
-// 26.3 and of sixteen 13.6.
-constexpr int kLamCols = 16, kLamSlots = 64;
-__global__ __launch_bounds__(kLamCols * kLamSlots) void bwd_dlam_kernel(BwdArgs a)
+// one workgroup per head and sixteen features (64 bytes of a row).  256 / d_k slots take the
+// (batch, chunk) entries in turn, each into eight running sums in turn (its last entries, fewer
+// than eight, into the first); the eight sums of a slot and then the slots are combined in a fixed
+// order.  Thread (sum, b) forms one running sum, sixteen loads in flight.  Bound by the round
+// trips of its loads: B8 H16 T2048 d128 4.8 us; 26.3 with all eight sums of a slot in one
+// thread and one workgroup per head.
+constexpr int kLamCols = 16, kLamAhead = 16;
+constexpr int kLamSums = 8;  // running sums of a slot
+template <int DK>
+__global__ __launch_bounds__(kLamCols * kLamSums * kThreads / DK) void bwd_dlam_kernel(BwdArgs a)
 {
+    constexpr int kSlots = kThreads / DK, kStep = kSlots * kLamSums, kParts = DK / kLamCols;
     const ForwardShape s = a.s;
-    const int dk = s.d_k, parts = dk / kLamCols;
-    const int64_t h = blockIdx.x / parts;
-    const int col = threadIdx.x % kLamCols, slot = threadIdx.x / kLamCols;
-    const int b = int(blockIdx.x % parts) * kLamCols + col;
-    const int64_t per = s.batch * s.n_chunks;  // partial sums of this head
-    __shared__ float sAcc[kLamCols * kLamSlots];
-    float acc8[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    for (int64_t e0 = slot; e0 < per; e0 += 8 * kLamSlots) {
-        float v[8];
+    const int64_t h = blockIdx.x / kParts;
+    const int col = threadIdx.x % kLamCols, sum = threadIdx.x / kLamCols;  // sum = slot + kSlots * (its place among the eight)
+    const int b = int(blockIdx.x % kParts) * kLamCols + col, slot = sum % kSlots;
+    const int nc = s.n_chunks, per = int(s.batch * nc);  // partial sums of this head (below 2^31: one workgroup each)
+    __shared__ float sAcc[kStep][kLamCols];
+    auto part = [&](int e) {
+        const int bb = int(unsigned(e) / unsigned(nc)), n = e - bb * nc;
+        return a.dlam_part[((int64_t(bb) * s.heads + h) * nc + n) * DK + b];
+    };
+    // passes over all eight sums of the slot, then its last entries
+    const int last = slot + (kLamSums - 1) * kSlots;
+    const int passes = per > last ? (per - 1 - last) / kStep + 1 : 0;
+    float acc = 0.0f;
+    for (int m0 = 0; m0 < passes; m0 += kLamAhead) {
+        float v[kLamAhead];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int64_t e = min<int64_t>(e0 + u * kLamSlots, per - 1);
-            const int64_t bb = e / s.n_chunks, n = e % s.n_chunks;
-            v[u] = a.dlam_part[((bb * s.heads + h) * s.n_chunks + n) * dk + b];
-        }
+        for (int u = 0; u < kLamAhead; ++u) v[u] = part(sum + min(m0 + u, passes - 1) * kStep);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc8[u] += e0 + u * kLamSlots < per ? v[u] : 0.0f;
+        for (int u = 0; u < kLamAhead; ++u)
+            if (m0 + u < passes) acc += v[u];
     }
-    sAcc[threadIdx.x] = ((acc8[0] + acc8[1]) + (acc8[2] + acc8[3])) + ((acc8[4] + acc8[5]) + (acc8[6] + acc8[7]));
+    if (sum < kSlots && per > 0) {
+        float v[kLamSums - 1];
+#pragma unroll
+        for (int u = 0; u < kLamSums - 1; ++u) v[u] = part(min(slot + passes * kStep + u * kSlots, per - 1));
+#pragma unroll
+        for (int u = 0; u < kLamSums - 1; ++u)
+            if (slot + passes * kStep + u * kSlots < per) acc += v[u];
+    }
+    sAcc[sum][col] = acc;
     __syncthreads();
-    if (slot == 0) {
+    if (sum == 0) {
         float t = 0.0f;
-        for (int u = 0; u < kLamSlots; ++u) t += sAcc[u * kLamCols + col];
-        a.dlam[h * dk + b] = t;
+        for (int u = 0; u < kSlots; ++u) {
+            auto at = [&](int i) { return sAcc[u + kSlots * i][col]; };
+            t += ((at(0) + at(1)) + (at(2) + at(3))) + ((at(4) + at(5)) + (at(6) + at(7)));
+        }
+        a.dlam[h * DK + b] = t;
     }
 }
 
@@ -1522,7 +1540,8 @@ hipError_t launch_bwd_dims(const BwdArgs& a, hipStream_t stream, int stage)
             hipLaunchKernelGGL((bwd_grad_kernel<Tin, DK, DV>), dim3(chunks), dim3(kGradThreads), 0, stream, a);
             break;
         default:
-            hipLaunchKernelGGL(bwd_dlam_kernel, dim3(unsigned(a.s.heads * (a.s.d_k / kLamCols))), dim3(kLamCols * kLamSlots), 0, stream, a);
+            hipLaunchKernelGGL(bwd_dlam_kernel<DK>, dim3(unsigned(a.s.heads * (DK / kLamCols))),
+                               dim3(kLamCols * kLamSums * kThreads / DK), 0, stream, a);
     }
     return hipGetLastError();
 }

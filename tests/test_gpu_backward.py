@@ -232,3 +232,34 @@ def test_lambda_gradient_sums_every_chunk(B, dk):
 
     want = sum(dlam(lo, min(lo + 4, B)) for lo in range(0, B, 4))
     assert rel_l2(dlam(0, B), want) <= TOL_F32
+
+
+@pytest.mark.parametrize("dk", [64, 128])
+@pytest.mark.parametrize("B", [1, 2, 7, 16, 33, 40, 131, 271])
+def test_lambda_gradient_sums_in_its_fixed_order(B, dk):
+    """dLambda adds the per-chunk partial sums in one order whatever the launch (256 / d_k slots, eight
+    running sums each, the slot's last entries to its first sum): sequences of one chunk, whose partial
+    sums are the dLambda of each alone, added here in fp32 in that order, bit for bit."""
+    T, H, n_cg = 20, 2, 3
+    g = torch.Generator(device="cuda").manual_seed(B + dk)
+    q, k = (torch.nn.functional.normalize(torch.randn((B, H, T, dk), generator=g, device="cuda"), dim=-1) for _ in range(2))
+    v, dout = (torch.randn((B, H, T, 64), generator=g, device="cuda") for _ in range(2))
+    gamma, beta = (torch.rand((B, H, T), generator=g, device="cuda") for _ in range(2))
+    lam = torch.rand((H, dk), generator=g, device="cuda") + 0.25
+
+    def dlam(i, j):
+        f = L.forward(q[i:j], k[i:j], v[i:j], gamma[i:j], beta[i:j], lam, n_cg, 64, L.MESA_PREC_F32, want_qstar=True)
+        return L.backward(k[i:j], v[i:j], gamma[i:j], beta[i:j], lam, f["qstar"], dout[i:j], n_cg)["dlam"].cpu().numpy()
+
+    part = [dlam(i, i + 1) for i in range(B)]
+    slots, want = 256 // dk, np.zeros((H, dk), np.float32)
+    for s in range(slots):
+        acc, e = [np.zeros((H, dk), np.float32) for _ in range(8)], s
+        while e + 7 * slots < B:
+            for u in range(8):
+                acc[u] = acc[u] + part[e + u * slots]
+            e += 8 * slots
+        for e in range(e, B, slots):
+            acc[0] = acc[0] + part[e]
+        want = want + (((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7])))
+    assert np.array_equal(dlam(0, B), want)
